@@ -24,7 +24,7 @@ struct BatchDesc {
     const T* E;
     const T* inv_s[2];
     const cpx<T>* K[2];
-    const cpx<T>* tw[2];
+    const cpx<T>* tw[2];    // per-pass twiddle layout of the schedule's radix
     int n1, n2;
     int logn[2];      // log2 of the transform length per direction
     int mode;         // 0 flat, 1 flat + layer, 2 curved
@@ -110,6 +110,7 @@ __device__ __forceinline__ void batch_tile(const BatchDesc<T>& d, int tile, int 
     p.K = d.K[dir];
     p.tw = d.tw[dir];
     p.n1 = d.n1;
+    p.pitch = d.n1;
     p.nlines = COLS ? d.n1 : d.n2;
     p.e_pre = COLS ? 0 : (k == 0 ? 1 : 2);
     p.e_post = COLS ? (k == d.steps - 1 ? 1 : 0) : 0;

@@ -102,7 +102,6 @@ static void fill_desc(BatchDesc<T>& d, const dirac_solver* s, int steps, const i
     for (int ax = 0; ax < 2; ++ax) {
         d.inv_s[ax] = reinterpret_cast<const T*>(base + s->lay.inv_s[ax]);   // ones without a layer
         d.K[ax] = reinterpret_cast<const cpx<T>*>(base + s->lay.K[ax]);
-        d.tw[ax] = reinterpret_cast<const cpx<T>*>(base + s->lay.tw[ax]);
     }
     d.n1 = s->g.n1;
     d.n2 = s->g.n2;
@@ -111,6 +110,9 @@ static void fill_desc(BatchDesc<T>& d, const dirac_solver* s, int steps, const i
     d.mode = s->curved ? 2 : (s->pml ? 1 : 0);
     d.sched[0] = sched[0][d.logn[0]];
     d.sched[1] = sched[1][d.logn[1]];
+    for (int ax = 0; ax < 2; ++ax)
+        d.tw[ax] = reinterpret_cast<const cpx<T>*>(
+            base + s->lay.twp[ax][twp_index(bsched_radix(1 << d.logn[ax], d.sched[ax]))]);
     d.steps = steps;
     d.e0u = cpx<T>{(T)s->e0u_re, (T)s->e0u_im};
 }

@@ -79,7 +79,7 @@ __global__ void __launch_bounds__(bis_threads(N, COLS)) bis_stage_kernel(BisPara
     if constexpr (PRELOAD_E) loadE();
     const cpx<T>* tw = p.tw;
     cpx<T> twv[TS::ON ? F::TW_ITER : 1];
-    if constexpr (TS::ON) F::tw_load(twv, p.tw, threadIdx.x);
+    if constexpr (TS::ON) F::template tw_load<false>(twv, p.tw, threadIdx.x);
     T b[R], k2[R], k1[R], dsym[R];
     cpx<T> ksym[R];
 #pragma unroll
@@ -136,7 +136,7 @@ __global__ void __launch_bounds__(bis_threads(N, COLS)) bis_stage_kernel(BisPara
         old[1][r] = v[1][r];
     }
 
-    F::template fft<false, TS::ON>(v, lds, c, tw);
+    F::template fft<false, true>(v, lds, c, tw);
     cpx<T> acc[2][R], t[2][R];
     // b (1 - b) (c dt)^2 / 2 * F^-1[xi^2 psi_hat]
 #pragma unroll
@@ -146,7 +146,7 @@ __global__ void __launch_bounds__(bis_threads(N, COLS)) bis_stage_kernel(BisPara
         t[0][s] = scal(w2, v[0][s]);
         t[1][s] = scal(w2, v[1][s]);
     }
-    F::template fft<true, TS::ON>(t, lds, c, tw);
+    F::template fft<true, true>(t, lds, c, tw);
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         acc[0][r] = scal(k2[r], t[0][r]);
@@ -160,7 +160,7 @@ __global__ void __launch_bounds__(bis_threads(N, COLS)) bis_stage_kernel(BisPara
             t[0][s] = mul_i(scal(d, v[0][s]));
             t[1][s] = mul_i(scal(d, v[1][s]));
         }
-        F::template fft<true, TS::ON>(t, lds, c, tw);
+        F::template fft<true, true>(t, lds, c, tw);
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             acc[0][r] = acc[0][r] + scal(k1[r], t[0][r]);
@@ -180,7 +180,7 @@ __global__ void __launch_bounds__(bis_threads(N, COLS)) bis_stage_kernel(BisPara
             v[1][s] = scal(k.re, a1) + scal(k.im, a0);
         }
     }
-    F::template fft<true, TS::ON>(v, lds, c, tw);
+    F::template fft<true, true>(v, lds, c, tw);
 #pragma unroll
     for (int r = 0; r < R; ++r) {
 #pragma unroll

@@ -179,7 +179,7 @@ __global__ void __launch_bounds__(em_threads(N, COLS)) em_stage_kernel(EmParams<
     }
     const cpx<T>* tw = p.tw;
     cpx<T> twv[TS::ON ? F::TW_ITER : 1];
-    if constexpr (TS::ON) F::tw_load(twv, p.tw, threadIdx.x);
+    if constexpr (TS::ON) F::template tw_load<false>(twv, p.tw, threadIdx.x);
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         b[r] = (T)a[r] * gld(p.inv_s + c.j + r * P);       // ones without a layer
@@ -196,7 +196,7 @@ __global__ void __launch_bounds__(em_threads(N, COLS)) em_stage_kernel(EmParams<
         old[0][r] = v[0][r];
         old[1][r] = v[1][r];
     }
-    F::template fft<false, TS::ON>(v, lds, c, tw);
+    F::template fft<false, true>(v, lds, c, tw);
 #pragma unroll
     for (int s = 0; s < R; ++s) {
         const cpx<T> k = ksym[s];
@@ -209,7 +209,7 @@ __global__ void __launch_bounds__(em_threads(N, COLS)) em_stage_kernel(EmParams<
             v[1][s] = scal(k.re, a1) + scal(k.im, a0);
         }
     }
-    F::template fft<true, TS::ON>(v, lds, c, tw);
+    F::template fft<true, true>(v, lds, c, tw);
     if (!valid) return;
 #pragma unroll
     for (int r = 0; r < R; ++r) {

@@ -81,7 +81,7 @@ __device__ __forceinline__ T gld(const T* p) { return *(const __attribute__((add
 template <typename T>
 __device__ __forceinline__ void gst(T* p, T v) { *(__attribute__((address_space(1))) T*)p = v; }
 // Device-scope write-through stores (buffer_store ... sc1) of 16 or 8 bytes at
-// byte offset `off` from the wave-uniform `base`: the line goes to memory at
+// byte offset `off` + `uoff` (uoff wave-uniform) from the wave-uniform `base`: the line goes to memory at
 // once instead of sitting dirty in this XCD's L2 until the end-of-dispatch
 // write-back.  Full-width stores, so a wave's contiguous stores still combine
 // into whole lines.  The resource's third dword is the gfx9 raw-buffer format;
@@ -92,11 +92,11 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t wt_rsrc(const void* base) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, 0x7fffffff, 0x00020000);
 }
 constexpr int kCacheSc1 = 16;      // cache-policy bit sc1 of the buffer intrinsics
-__device__ __forceinline__ void gst_wt16(const void* base, uint32_t off, u32x4 v) {
-    __builtin_amdgcn_raw_buffer_store_b128(v, wt_rsrc(base), (int)off, 0, kCacheSc1);
+__device__ __forceinline__ void gst_wt16(const void* base, uint32_t off, u32x4 v, uint32_t uoff = 0) {
+    __builtin_amdgcn_raw_buffer_store_b128(v, wt_rsrc(base), (int)off, (int)uoff, kCacheSc1);
 }
-__device__ __forceinline__ void gst_wt8(const void* base, uint32_t off, u32x2 v) {
-    __builtin_amdgcn_raw_buffer_store_b64(v, wt_rsrc(base), (int)off, 0, kCacheSc1);
+__device__ __forceinline__ void gst_wt8(const void* base, uint32_t off, u32x2 v, uint32_t uoff = 0) {
+    __builtin_amdgcn_raw_buffer_store_b64(v, wt_rsrc(base), (int)off, (int)uoff, kCacheSc1);
 }
 __device__ __forceinline__ cpx<float> gld(const cpx<float>* p) {
     const f2v v = gld(reinterpret_cast<const f2v*>(p));
@@ -153,6 +153,22 @@ __host__ __device__ constexpr int ilog(int n, int r) {  // largest e with r^e | 
     return e;
 }
 __host__ __device__ constexpr int ipow(int r, int e) { int v = 1; for (int i = 0; i < e; ++i) v *= r; return v; }
+
+// Entry e of the per-pass twiddle layout of a radix-R line of n points (see
+// LineFFT) as an index m into the plain table exp(-2 pi i m / n); -1 past its
+// end, and for every e when n has no radix-R schedule of two or more passes.
+__host__ __device__ inline int tw_pass_src(int n, int R, int e) {
+    const int ex = ilog(n, R), rem = n / ipow(R, ex);
+    if (ex < 2) return -1;
+    int ns = R;
+    for (int p = 1; p < ex + (rem > 1 ? 1 : 0); ++p) {
+        const int rp = p == 1 && rem > 1 ? rem : R;
+        if (e < ns * (rp - 1)) return (e / ns + 1) * (e % ns) * (n / (ns * rp));
+        e -= ns * (rp - 1);
+        ns *= rp;
+    }
+    return -1;
+}
 
 // Largest LDS exchange buffer (bytes) that holds both spinor components of a
 // tile at once; larger tiles of threads carrying both exchange them one at a time.
@@ -254,12 +270,12 @@ struct LineFFT {
     }
     __device__ static __forceinline__ int slot(const Coord& c, int cc) { return CPT == 1 ? c.comp : cc; }
 
-    // Per-pass twiddle layout (for tables staged in LDS).  Pass p >= 1 reads
-    // W_N^{r k N / (Ns Rp)} for k = jj mod Ns and r = 1..Rp-1; the plain table
-    // W_N^m read at m = r k N / (Ns Rp) puts the distinct k of a wave a multiple
-    // of 32 banks apart (up to 8-way conflicts).  Stored per pass as
-    // [k][r - 1] instead, neighbouring k sit Rp - 1 (odd) entries apart, so a
-    // wave's reads fall on distinct banks.  Entry count: sum_p Ns_p (Rp - 1) < N.
+    // Per-pass twiddle layout.  Pass p >= 1 reads W_N^{r k N / (Ns Rp)} for
+    // k = jj mod Ns and r = 1..Rp-1; in the plain table W_N^m neighbouring k sit
+    // r N / (Ns Rp) entries apart (a gather over up to 60 cache lines for one
+    // wave's read of a global table, up to 8-way bank conflicts in LDS).  Stored
+    // per pass as [r - 1][k], a wave reads consecutive entries.  Entry count:
+    // sum_p Ns_p (Rp - 1) < N.
     __host__ __device__ static constexpr int tw_off(int p) {
         int o = 0;
         for (int q = 1; q < p; ++q) o += ns_of(q) * (radix_of(q) - 1);
@@ -276,20 +292,21 @@ struct LineFFT {
             constexpr int Rp = radix_of(PASS), Ns = ns_of(PASS), off = tw_off(PASS);
             if (e < off + Ns * (Rp - 1)) {
                 const int q = e - off;
-                return (q % (Rp - 1) + 1) * (q / (Rp - 1)) * (N / (Ns * Rp));
+                return (q / Ns + 1) * (q % Ns) * (N / (Ns * Rp));
             }
             return tw_src<PASS + 1>(e);
         }
     }
-    // Gather the per-pass layout from the plain table tw[m] = exp(-2 pi i m / N):
+    // Stage the per-pass layout in LDS, from the plain table tw[m] =
+    // exp(-2 pi i m / N) (GATHER) or from a table already in that layout:
     // tw_load issues the loads (thread t takes entries t + i NT), tw_store
     // writes them to LDS once they have arrived.
+    template <bool GATHER = true>
     __device__ static __forceinline__ void tw_load(cpx<T> (&reg)[TW_ITER], const cpx<T>* tw, int t) {
 #pragma unroll
         for (int i = 0; i < TW_ITER; ++i) {
-            const int e = t + i * NT;
-            const int src = tw_src<1>(TW_ENTRIES % NT == 0 || e < TW_ENTRIES ? e : TW_ENTRIES - 1);
-            reg[i] = gld(tw + src);
+            const int e = t + i * NT, ec = TW_ENTRIES % NT == 0 || e < TW_ENTRIES ? e : TW_ENTRIES - 1;
+            reg[i] = gld(tw + (GATHER ? tw_src<1>(ec) : ec));
         }
     }
     __device__ static __forceinline__ void tw_store(const cpx<T> (&reg)[TW_ITER], cpx<T>* twl, int t) {
@@ -343,7 +360,7 @@ struct LineFFT {
             const int k = jj % Ns;
 #pragma unroll
             for (int r = 1; r < Rp; ++r) {
-                const cpx<T> w = PP ? tw[tw_off(PASS) + k * (Rp - 1) + (r - 1)] : tw[r * k * (N / (Ns * Rp))];
+                const cpx<T> w = PP ? tw[tw_off(PASS) + (r - 1) * Ns + k] : tw[r * k * (N / (Ns * Rp))];
 #pragma unroll
                 for (int cc = 0; cc < CPT; ++cc)
                     v[cc][t * Rp + r] = INV ? cmulc(v[cc][t * Rp + r], w) : cmul(v[cc][t * Rp + r], w);

@@ -193,6 +193,7 @@ Layout make_layout(const dirac_grid* g, const dirac_metric* m, const dirac_pml* 
         L.K[ax] = take(n * 2 * sz);
         L.D[ax] = take(n * sz);
         L.tw[ax] = take(n * 2 * sz);
+        for (size_t& t : L.twp[ax]) t = take(n * 2 * sz);
     }
     const size_t setup_parts = ((N + 255) / 256) * 3;
     const size_t obs_parts = ((size_t)g->n1 + g->n2) * 8;
@@ -279,8 +280,9 @@ const KernelEntry* pick_entry(int prec, int n, int dir, int other, int mode) {
 
 // ---------------------------------------------------------------- launches
 
+// radix: of the kernel launched (its twiddle layout)
 template <typename T>
-StageParams<T> stage_params(const dirac_solver* s, int dir, int e_pre, int e_post) {
+StageParams<T> stage_params(const dirac_solver* s, int dir, int radix, int e_pre, int e_post) {
     StageParams<T> p{};
     char* b = s->base;
     p.psi = reinterpret_cast<T*>(b + s->lay.psi);
@@ -289,8 +291,9 @@ StageParams<T> stage_params(const dirac_solver* s, int dir, int e_pre, int e_pos
     p.E = s->curved ? reinterpret_cast<const T*>(b + s->lay.E) : nullptr;
     p.inv_s = reinterpret_cast<const T*>(b + s->lay.inv_s[dir]);     // ones without a layer
     p.K = reinterpret_cast<const cpx<T>*>(b + s->lay.K[dir]);
-    p.tw = reinterpret_cast<const cpx<T>*>(b + s->lay.tw[dir]);
+    p.tw = reinterpret_cast<const cpx<T>*>(b + s->lay.twp[dir][twp_index(radix)]);
     p.n1 = s->g.n1;
+    p.pitch = s->g.n1;
     p.nlines = dir == 0 ? s->g.n2 : s->g.n1;
     assert(dir == 0 || e_pre == 0);                 // Step 1 belongs to the row launch
     p.e_pre = e_pre;
@@ -304,7 +307,7 @@ template <typename T>
 BisParams<T> bis_params(const dirac_solver* s, int dir, int e_pre, int e_post) {
     BisParams<T> p{};
     char* b = s->base;
-    p.s = stage_params<T>(s, dir, e_pre, e_post);
+    p.s = stage_params<T>(s, dir, kBisRadix, e_pre, e_post);
     p.da = s->lay.da != SIZE_MAX ? reinterpret_cast<const T*>(b + s->lay.da) : nullptr;
     p.D = reinterpret_cast<const T*>(b + s->lay.D[dir]);
     p.hh = (T)(0.5 * (s->g.c * s->g.dt) * (s->g.c * s->g.dt));
@@ -315,7 +318,7 @@ BisParams<T> bis_params(const dirac_solver* s, int dir, int e_pre, int e_post) {
 template <typename T>
 EmParams<T> em_params(const dirac_solver* s, int dir, int e_pre, int e_post, int64_t step) {
     EmParams<T> p{};
-    p.s = stage_params<T>(s, dir, e_pre, e_post);
+    p.s = stage_params<T>(s, dir, em_radix(dir == 0 ? s->g.n1 : s->g.n2), e_pre, e_post);
     p.rec = reinterpret_cast<const T*>(s->base + s->lay.em);
     // Step 1 of step n (and Step 5 of step n - 1 before it) and Step 5 of step n
     // evaluate the potentials at t_{n+1/2} (resp. t_{n-1/2})
@@ -408,11 +411,11 @@ Launch make_launch(const dirac_solver* s, int dir, int e_pre, int e_post, int64_
     L.grid = dim3((nlines + e->lines - 1) / e->lines);
     L.block = dim3(e->nthreads);
     if (s->prec == DIRAC_FP64) {
-        auto p = stage_params<double>(s, dir, e_pre, e_post);
+        auto p = stage_params<double>(s, dir, e->radix, e_pre, e_post);
         std::memcpy(L.params, &p, sizeof p);
         L.psize = sizeof p;
     } else {
-        auto p = stage_params<float>(s, dir, e_pre, e_post);
+        auto p = stage_params<float>(s, dir, e->radix, e_pre, e_post);
         std::memcpy(L.params, &p, sizeof p);
         L.psize = sizeof p;
     }
@@ -678,6 +681,7 @@ dirac_status dirac_create_solver(const dirac_grid* g, const dirac_metric* m, con
         ap.K = b + lay.K[ax];
         ap.D = b + lay.D[ax];
         ap.tw = b + lay.tw[ax];
+        for (int i = 0; i < 3; ++i) ap.twp[i] = b + lay.twp[ax][i];
         hipError_t e = launch_setup_axis(ap, s->stream);
         if (e != hipSuccess) return bail(hip_fail(e, "setup axis tables"));
     }
@@ -797,6 +801,7 @@ static dirac_status observables_into(dirac_solver* s, dirac_obs* out, double* pa
         p.fV = envelope_at(s->env_V, t);
     }
     p.n1 = s->g.n1; p.n2 = s->g.n2;
+    p.pitch = s->g.n1;
     p.a1 = s->g.a1; p.a2 = s->g.a2;
     p.h1 = 2.0 * s->g.a1 / s->g.n1; p.h2 = 2.0 * s->g.a2 / s->g.n2;
     size_t need = 0;

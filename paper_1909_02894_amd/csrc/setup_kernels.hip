@@ -2,6 +2,7 @@
 // state conversions, and the fixed-order final reduction of the observables.
 #include <hip/hip_runtime.h>
 #include <math.h>
+#include "fft_line.hpp"
 #include "setup_kernels.hpp"
 
 namespace dirac {
@@ -62,6 +63,20 @@ __global__ void setup_axis_kernel(SetupAxisParams p) {
         put<double>(p.D, k, xi * inv_n);
         put<double>(p.tw, 2 * k, tc);
         put<double>(p.tw, 2 * k + 1, -ts);
+    }
+    // entry k of the per-pass layouts: the same FP64 values as the plain table
+    for (int i = 0; i < 3; ++i) {
+        if (!p.twp[i]) continue;
+        const int m = tw_pass_src(n, 4 << i, k);
+        double s = 0.0, c = 1.0;
+        if (m >= 0) sincospi(2.0 * m / n, &s, &c);
+        if (p.fp32) {
+            put<float>(p.twp[i], 2 * k, c);
+            put<float>(p.twp[i], 2 * k + 1, -s);
+        } else {
+            put<double>(p.twp[i], 2 * k, c);
+            put<double>(p.twp[i], 2 * k + 1, -s);
+        }
     }
 }
 

@@ -17,6 +17,7 @@ struct SetupAxisParams {
     void* K;       // n complex: (cos, sin)(c dt xi) / n
     void* D;       // n reals: xi / n
     void* tw;      // n complex: exp(-2 pi i k / n)
+    void* twp[3];  // n complex each: the per-pass twiddle layouts of radix 4, 8, 16 (or null)
 };
 
 struct SetupPointParams {

@@ -26,6 +26,7 @@ struct Layout {
     size_t K[2];       // directional symbols per axis (complex T)
     size_t D[2];       // derivative symbols per axis (T)
     size_t tw[2];      // FFT twiddles per axis (complex T)
+    size_t twp[2][3];  // per-pass twiddle layouts per axis, radix 4, 8, 16 (complex T)
     size_t cn_vec;     // Scheme I: 2 sets of gmres_restart + 4 FP64 vectors (rhs, operator product x / y
                        // parts, basis), then a second state vector
     size_t cn_part;    // Scheme I: reduction partials
@@ -47,6 +48,8 @@ dirac_status cn_step_n(dirac_solver* s, int64_t nsteps);
 // Whether a solve with potentials runs its exponentials as a pointwise pass
 // (plain direction kernels) rather than inside the direction kernels.
 bool em_pass(const dirac_solver* s);
+// Index of a schedule's radix (4, 8, 16) in Layout::twp.
+constexpr int twp_index(int radix) { return radix == 4 ? 0 : radix == 8 ? 1 : 2; }
 const KernelEntry* pick_entry(int prec, int n, int dir, int other, int mode);
 
 }  // namespace dirac

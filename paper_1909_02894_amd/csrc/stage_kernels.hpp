@@ -21,14 +21,15 @@ namespace dirac {
 
 template <typename T>
 struct StageParams {
-    T* psi;                      // state, 4 T per point, row pitch n1 points
+    T* psi;                      // state, 4 T per point, row pitch `pitch` points
     const T* a;                  // a(x) per point along this direction's lines (row-major for x,
                                  // the transposed table for y: a[line * n + pos]), or null (a = 1)
     const T* E;                  // half-step exponential per point (e0 re, im, e1 re, im), or null
     const T* inv_s;              // 1/S along the line direction (n entries; ones without a layer)
     const cpx<T>* K;             // symbol per mode, already scaled by 1/n
-    const cpx<T>* tw;            // exp(-2 pi i k / n), k < n
-    int n1;                      // points per row
+    const cpx<T>* tw;            // exp(-2 pi i m / n) in the per-pass layout of the kernel's radix
+    int n1;                      // points per row (pitch of the E table)
+    int pitch;                   // points from one state row to the next (>= n1)
     int nlines;                  // lines of this direction
     int e_pre;                   // Step-1 exponentials applied before the transform: 1 or 2 in
                                  // direction-x launches (which load E up front; 0 in the flat
@@ -53,6 +54,7 @@ struct ObsParams {
     const void* tw;              // twiddles (cpx<T>)
     double* partials;            // 8 doubles per workgroup
     int n1, n2;
+    int pitch;                   // points from one state row to the next
     int nlines;
     double a1, a2, h1, h2;
 };
@@ -67,10 +69,11 @@ template <typename T>
 __device__ __forceinline__ T ld_nt(const T* p) {
     return __builtin_nontemporal_load((const __attribute__((address_space(1))) T*)p);
 }
+// base advanced by a wave-uniform number of elements: a scalar addition, so that
+// the R accesses of a thread share one vector offset (its lane part) instead of
+// holding R of them (n = 4096 FP32 columns: 22 VGPRs fewer).
 template <typename T>
-__device__ __forceinline__ const T* at(const T* base, uint32_t elem) {
-    return reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) + elem * (uint32_t)sizeof(T));
-}
+__device__ __forceinline__ T* upt(T* base, uint32_t elems) { return base + (size_t)elems; }
 
 // One spinor component of a point (component c at byte offset c * 2 sizeof(T)).
 template <typename T>
@@ -97,36 +100,38 @@ constexpr int kStoreWtMaxColN = 1024;
 
 // WT: device-scope write-through stores (gst_wt16 / gst_wt8) instead of
 // ordinary ones; p must be wave-uniform then (the kernel's state pointer).
+// The point is idx + uidx (uidx wave-uniform).
 template <typename T, bool WT = false>
-__device__ __forceinline__ void store_point(T* p, uint32_t idx, cpx<T> u, cpx<T> v) {
-    const uint32_t off = idx * (uint32_t)(4 * sizeof(T));
-    char* b = reinterpret_cast<char*>(p) + off;
+__device__ __forceinline__ void store_point(T* p, uint32_t idx, cpx<T> u, cpx<T> v, uint32_t uidx = 0) {
+    const uint32_t off = idx * (uint32_t)(4 * sizeof(T)), uoff = uidx * (uint32_t)(4 * sizeof(T));
+    char* b = reinterpret_cast<char*>(upt(p, 4 * uidx)) + off;
     if constexpr (sizeof(T) == 8) {
         const d2v a{u.re, u.im}, c{v.re, v.im};
         if constexpr (WT) {
-            gst_wt16(p, off, __builtin_bit_cast(u32x4, a));
-            gst_wt16(p, off + 16, __builtin_bit_cast(u32x4, c));
+            gst_wt16(p, off, __builtin_bit_cast(u32x4, a), uoff);
+            gst_wt16(p, off + 16, __builtin_bit_cast(u32x4, c), uoff);
         } else {
             gst(reinterpret_cast<d2v*>(b), a);
             gst(reinterpret_cast<d2v*>(b) + 1, c);
         }
     } else {
         const f4v a{u.re, u.im, v.re, v.im};
-        if constexpr (WT) gst_wt16(p, off, __builtin_bit_cast(u32x4, a));
+        if constexpr (WT) gst_wt16(p, off, __builtin_bit_cast(u32x4, a), uoff);
         else gst(reinterpret_cast<f4v*>(b), a);
     }
 }
 template <typename T, bool WT = false>
-__device__ __forceinline__ void store_comp(T* p, uint32_t idx, int c, cpx<T> v) {
+__device__ __forceinline__ void store_comp(T* p, uint32_t idx, int c, cpx<T> v, uint32_t uidx = 0) {
     const uint32_t off = idx * (uint32_t)(4 * sizeof(T)) + c * (uint32_t)(2 * sizeof(T));
-    char* b = reinterpret_cast<char*>(p) + off;
+    const uint32_t uoff = uidx * (uint32_t)(4 * sizeof(T));
+    char* b = reinterpret_cast<char*>(upt(p, 4 * uidx)) + off;
     if constexpr (sizeof(T) == 8) {
         const d2v a{v.re, v.im};
-        if constexpr (WT) gst_wt16(p, off, __builtin_bit_cast(u32x4, a));
+        if constexpr (WT) gst_wt16(p, off, __builtin_bit_cast(u32x4, a), uoff);
         else gst(reinterpret_cast<d2v*>(b), a);
     } else {
         const f2v a{v.re, v.im};
-        if constexpr (WT) gst_wt8(p, off, __builtin_bit_cast(u32x2, a));
+        if constexpr (WT) gst_wt8(p, off, __builtin_bit_cast(u32x2, a), uoff);
         else gst(reinterpret_cast<f2v*>(b), a);
     }
 }
@@ -172,12 +177,14 @@ __device__ __forceinline__ void stage_tile(const StageParams<T>& p, int tile, cp
     // loads read a clamped line (always in bounds, results unused past the
     // last line) so that they carry no branches; stores are guarded
     const int lline = valid ? line : p.nlines - 1;
-    const uint32_t n1 = (uint32_t)p.n1;
-    auto gidx = [&](int ln, int pos) -> uint32_t {
-        return COLS ? (uint32_t)pos * n1 + ln : (uint32_t)ln * n1 + pos;
-    };
+    const uint32_t pitch = (uint32_t)p.pitch, n1 = (uint32_t)p.n1;
+    // Point r of this thread sits at position c.j + r P of its line: a lane part
+    // (line, c.j) plus a wave-uniform part r P, which goes into the scalar base.
+    const uint32_t sln = COLS ? (uint32_t)c.j * pitch + lline : (uint32_t)lline * pitch + c.j;   // state
+    const uint32_t eln = COLS ? (uint32_t)c.j * n1 + lline : (uint32_t)lline * n1 + c.j;         // E table
     // the a table is laid out along this direction's lines (transposed for columns)
-    auto aidx = [&](int ln, int pos) -> uint32_t { return (uint32_t)ln * N + pos; };
+    const uint32_t aln = (uint32_t)lline * N + c.j;
+    const uint32_t sstep = COLS ? P * pitch : P, estep = COLS ? P * n1 : P;
     // v[cc][r] <- f(own, other, component, r) for every carried component
     auto mix = [&](cpx<T> (&a)[CPT][R], auto&& f) {
 #pragma unroll
@@ -199,9 +206,9 @@ __device__ __forceinline__ void stage_tile(const StageParams<T>& p, int tile, cp
     cpx<T> v[CPT][R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        const uint32_t q = gidx(lline, c.j + r * P);
-        if constexpr (CPT == 1) v[0][r] = load_comp(p.psi, q, c.comp);
-        else load_point(p.psi, q, v[0][r], v[1][r]);
+        const T* q = upt(p.psi, 4 * (r * sstep));
+        if constexpr (CPT == 1) v[0][r] = load_comp(q, sln, c.comp);
+        else load_point(q, sln, v[0][r], v[1][r]);
     }
     // Step 1 (and Step 5 of the previous step): row `comp` of
     // E = [[e0, e1], [conj e1, conj e0]]: A own + B other with A = e0, B = e1 for
@@ -213,7 +220,7 @@ __device__ __forceinline__ void stage_tile(const StageParams<T>& p, int tile, cp
     auto loadE = [&]() {
         if constexpr (MODE == 2) {
 #pragma unroll
-            for (int r = 0; r < R; ++r) load_point(p.E, gidx(lline, c.j + r * P), e0[r], e1[r]);
+            for (int r = 0; r < R; ++r) load_point(upt(p.E, 4 * (r * estep)), eln, e0[r], e1[r]);
         }
     };
     auto applyE = [&](int times) {
@@ -233,7 +240,7 @@ __device__ __forceinline__ void stage_tile(const StageParams<T>& p, int tile, cp
     if constexpr (PRELOAD_E) loadE();
     const cpx<T>* tw = p.tw;
     cpx<T> twv[TS::ON ? F::TW_ITER : 1];
-    if constexpr (TS::ON) F::tw_load(twv, p.tw, threadIdx.x);
+    if constexpr (TS::ON) F::template tw_load<false>(twv, p.tw, threadIdx.x);
     // blend weight b = a(x) / S(x^i) (MODE 2) or 1 / S(x^i) (MODE 1); the 1/S
     // table is always present in blended modes (ones without a layer)
     cpx<T> kk[PF ? R : 1];
@@ -242,19 +249,19 @@ __device__ __forceinline__ void stage_tile(const StageParams<T>& p, int tile, cp
         if constexpr (BLEND) {
 #pragma unroll
             for (int r = 0; r < R; ++r) {
-                const T sv = gld(p.inv_s + c.j + r * P);
+                const T sv = ld_at(p.inv_s + r * P, (uint32_t)c.j);
                 // columns of 4096+ points (states beyond the Infinity Cache) read a with
                 // a streaming load, which keeps it from evicting the partly written row
                 // segments of neighbouring column tiles; shorter lines keep it cached
                 // (curved FP64 2048² columns: 113 us cached, 133 us streamed)
-                if constexpr (MODE == 2 && COLS && N >= 4096) bb[r] = ld_nt(p.a + aidx(lline, c.j + r * P)) * sv;
-                else bb[r] = MODE == 2 ? ld_at(p.a, aidx(lline, c.j + r * P)) * sv : sv;
+                if constexpr (MODE == 2 && COLS && N >= 4096) bb[r] = ld_nt(p.a + r * P + aln) * sv;
+                else bb[r] = MODE == 2 ? ld_at(p.a + r * P, aln) * sv : sv;
             }
         }
     };
     if constexpr (PF) {
 #pragma unroll
-        for (int s = 0; s < R; ++s) kk[s] = gld(p.K + c.j + s * P);
+        for (int s = 0; s < R; ++s) kk[s] = ld_at(p.K + s * P, (uint32_t)c.j);
         blend_weights();
     }
     if constexpr (TS::ON) {
@@ -284,26 +291,26 @@ __device__ __forceinline__ void stage_tile(const StageParams<T>& p, int tile, cp
             for (int r = 0; r < R; ++r) old[cc][r] = v[cc][r];
     }
 
-    F::template fft<false, TS::ON>(v, lds, c, tw);
+    F::template fft<false, true>(v, lds, c, tw);
     mix(v, [&](cpx<T> own, cpx<T> other, int comp, int s) {
         cpx<T> k;
         if constexpr (PF) k = kk[s];
-        else k = gld(p.K + c.j + s * P);               // (cos, sin) / n
+        else k = ld_at(p.K + s * P, (uint32_t)c.j);    // (cos, sin) / n
         if constexpr (!COLS) {                         // K_x = cos I - i sin sigma_x
             return scal(k.re, own) + mul_mi(scal(k.im, other));
         } else {                                       // K_y = [[cos, -sin], [sin, cos]]
             return scal(k.re, own) - scal(comp ? -k.im : k.im, other);
         }
     });
-    F::template fft<true, TS::ON>(v, lds, c, tw);
+    F::template fft<true, true>(v, lds, c, tw);
 
     if constexpr (BLEND) {
         if constexpr (REREAD) {
 #pragma unroll
             for (int r = 0; r < R; ++r) {
-                const uint32_t q = gidx(lline, c.j + r * P);
-                if constexpr (CPT == 1) old[0][r] = load_comp(p.psi, q, c.comp);
-                else load_point(p.psi, q, old[0][r], old[1][r]);
+                const T* q = upt(p.psi, 4 * (r * sstep));
+                if constexpr (CPT == 1) old[0][r] = load_comp(q, sln, c.comp);
+                else load_point(q, sln, old[0][r], old[1][r]);
             }
         }
         if constexpr (!PF) blend_weights();
@@ -325,16 +332,14 @@ __device__ __forceinline__ void stage_tile(const StageParams<T>& p, int tile, cp
     if ((!COLS || N <= kStoreWtMaxColN) && p.wt) {
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            const uint32_t q = gidx(line, c.j + r * P);
-            if constexpr (CPT == 1) store_comp<T, true>(p.psi, q, c.comp, v[0][r]);
-            else store_point<T, true>(p.psi, q, v[0][r], v[1][r]);
+            if constexpr (CPT == 1) store_comp<T, true>(p.psi, sln, c.comp, v[0][r], r * sstep);
+            else store_point<T, true>(p.psi, sln, v[0][r], v[1][r], r * sstep);
         }
     } else {
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            const uint32_t q = gidx(line, c.j + r * P);
-            if constexpr (CPT == 1) store_comp(p.psi, q, c.comp, v[0][r]);
-            else store_point(p.psi, q, v[0][r], v[1][r]);
+            if constexpr (CPT == 1) store_comp(p.psi, sln, c.comp, v[0][r], r * sstep);
+            else store_point(p.psi, sln, v[0][r], v[1][r], r * sstep);
         }
     }
 }
@@ -400,16 +405,17 @@ obs_kernel(ObsParams p) {
     const cpx<T>* tw = static_cast<const cpx<T>*>(p.tw);
 
     cpx<T> v[CPT][R], old[CPT][R];
-    uint32_t idx[R];
+    uint32_t idx[R];                                       // of the observable planes
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         const int pos = c.j + r * P;
         idx[r] = COLS ? (uint32_t)pos * (uint32_t)p.n1 + line : (uint32_t)line * (uint32_t)p.n1 + pos;
+        const uint32_t q = COLS ? (uint32_t)pos * (uint32_t)p.pitch + line : (uint32_t)line * (uint32_t)p.pitch + pos;
         if constexpr (CPT == 1) {
-            v[0][r] = valid ? load_comp(psi, idx[r], c.comp) : cpx<T>{0, 0};
+            v[0][r] = valid ? load_comp(psi, q, c.comp) : cpx<T>{0, 0};
         } else {
             v[0][r] = v[1][r] = cpx<T>{0, 0};
-            if (valid) load_point(psi, idx[r], v[0][r], v[1][r]);
+            if (valid) load_point(psi, q, v[0][r], v[1][r]);
         }
 #pragma unroll
         for (int cc = 0; cc < CPT; ++cc) old[cc][r] = v[cc][r];
