@@ -556,10 +556,9 @@ dirac_status dirac_batch_autotune(dirac_batch* b, int32_t reps) {
     const bool graph_was = b->use_graph;
     b->use_graph = false;
     batch_drop_graph(b);
-    const size_t sz = b->prec == DIRAC_FP32 ? 4 : 8;
     for (int i : occ) {
         dirac_solver* s = b->slots[i];
-        const size_t bytes = (size_t)s->g.n1 * s->g.n2 * 4 * sz;
+        const size_t bytes = s->lay.psi_bytes;
         BTRY(hipMemcpyAsync(s->base + s->lay.scratch, s->base + s->lay.psi, bytes, hipMemcpyDeviceToDevice, b->stream),
              "save state");
     }
@@ -609,7 +608,7 @@ dirac_status dirac_batch_autotune(dirac_batch* b, int32_t reps) {
     }
     for (int i : occ) {
         dirac_solver* s = b->slots[i];
-        const size_t bytes = (size_t)s->g.n1 * s->g.n2 * 4 * sz;
+        const size_t bytes = s->lay.psi_bytes;
         BTRY(hipMemcpyAsync(s->base + s->lay.psi, s->base + s->lay.scratch, bytes, hipMemcpyDeviceToDevice, b->stream),
              "restore state");
     }

@@ -261,6 +261,20 @@ __global__ void f32_to_c128_kernel(const float* src, double* dst, size_t count) 
         dst[i] = (double)src[i];
 }
 
+// Rows of 2^lg pairs of reals between two row pitches (in reals; both even).
+// Bound by memory: 4096^2 FP32 rows widened in 0.2 ms against the ~10 ms of
+// their download.
+template <typename S, typename D>
+__global__ void copy_rows_kernel(const S* src, size_t spitch, D* dst, size_t dpitch, int lg, size_t pairs) {
+    struct alignas(2 * sizeof(S)) S2 { S a, b; };
+    struct alignas(2 * sizeof(D)) D2 { D a, b; };
+    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < pairs; i += (size_t)gridDim.x * blockDim.x) {
+        const size_t row = i >> lg, col = 2 * (i & (((size_t)1 << lg) - 1));
+        const S2 v = *reinterpret_cast<const S2*>(src + row * spitch + col);
+        *reinterpret_cast<D2*>(dst + row * dpitch + col) = D2{(D)v.a, (D)v.b};
+    }
+}
+
 // Fixed-order sum of nparts 8-double partial records: thread t adds records
 // t, t + 256, ... in order, then a fixed tree.  One workgroup of 256 threads.
 __global__ void reduce_partials_kernel(const double* part, int nparts, double* out) {
@@ -336,6 +350,25 @@ hipError_t launch_c128_to_f32(const double* src, float* dst, size_t count, hipSt
 hipError_t launch_f32_to_c128(const float* src, double* dst, size_t count, hipStream_t s) {
     hipLaunchKernelGGL(f32_to_c128_kernel, dim3(1024), dim3(256), 0, s, src, dst, count);
     return hipGetLastError();
+}
+template <typename S, typename D>
+static hipError_t copy_rows(const S* src, size_t spitch, D* dst, size_t dpitch, size_t len, size_t rows,
+                            hipStream_t s) {
+    hipLaunchKernelGGL((copy_rows_kernel<S, D>), dim3(2048), dim3(256), 0, s, src, spitch, dst, dpitch,
+                       __builtin_ctzll(len / 2), rows * (len / 2));
+    return hipGetLastError();
+}
+hipError_t launch_copy_rows(const double* src, size_t spitch, float* dst, size_t dpitch, size_t len, size_t rows,
+                            hipStream_t s) {
+    return copy_rows(src, spitch, dst, dpitch, len, rows, s);
+}
+hipError_t launch_copy_rows(const float* src, size_t spitch, double* dst, size_t dpitch, size_t len, size_t rows,
+                            hipStream_t s) {
+    return copy_rows(src, spitch, dst, dpitch, len, rows, s);
+}
+hipError_t launch_copy_rows(const double* src, size_t spitch, double* dst, size_t dpitch, size_t len, size_t rows,
+                            hipStream_t s) {
+    return copy_rows(src, spitch, dst, dpitch, len, rows, s);
 }
 hipError_t launch_reduce_partials(const double* part, int nparts, double* out, hipStream_t s) {
     hipLaunchKernelGGL(reduce_partials_kernel, dim3(1), dim3(256), 0, s, part, nparts, out);

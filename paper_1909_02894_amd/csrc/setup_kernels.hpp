@@ -46,6 +46,14 @@ hipError_t launch_setup_points(const SetupPointParams& p, double* fold_out, hipS
 hipError_t launch_transpose(const void* in, void* out, int n1, int n2, int elem, hipStream_t s);
 hipError_t launch_c128_to_f32(const double* src, float* dst, size_t count, hipStream_t s);
 hipError_t launch_f32_to_c128(const float* src, double* dst, size_t count, hipStream_t s);
+// Copy `rows` rows of `len` reals (a power of two) between arrays whose rows start
+// `spitch` / `dpitch` reals apart, converting between precisions.
+hipError_t launch_copy_rows(const double* src, size_t spitch, float* dst, size_t dpitch, size_t len, size_t rows,
+                            hipStream_t s);
+hipError_t launch_copy_rows(const float* src, size_t spitch, double* dst, size_t dpitch, size_t len, size_t rows,
+                            hipStream_t s);
+hipError_t launch_copy_rows(const double* src, size_t spitch, double* dst, size_t dpitch, size_t len, size_t rows,
+                            hipStream_t s);
 hipError_t launch_reduce_partials(const double* part, int nparts, double* out, hipStream_t s);
 
 }  // namespace dirac

@@ -13,7 +13,9 @@ namespace dirac {
 // Byte offsets of every region inside the caller's device buffer (256-aligned).
 // SIZE_MAX marks a region the solve does not need.
 struct Layout {
-    size_t psi;        // state, n1 n2 points x 2 components x complex (T)
+    size_t psi;        // state, n2 rows of `pitch` points x 2 components x complex (T)
+    size_t psi_bytes;  // bytes of the state region (its row padding included)
+    int pitch;         // points from one state row to the next (state_pitch)
     size_t a;          // a(x) per point (T), curved metrics only
     size_t aT;         // the same, transposed ([n1][n2]: contiguous along columns), for the y direction
     size_t E;          // Step-1 exponential per point, 4 T (curved only)
@@ -21,7 +23,7 @@ struct Layout {
     size_t em;         // per-point record of the time-dependent exponential, 8 T (potentials only)
     size_t obs;        // 5 FP64 planes for the observables
     size_t fields;     // FIELDS metric staging, 6 FP64 planes
-    size_t scratch;    // n1 n2 x 32 bytes: complex128 staging / autotune save
+    size_t scratch;    // complex128 staging (n1 n2 x 32 bytes) / autotune save (psi_bytes)
     size_t inv_s[2];   // 1/S per axis (T)
     size_t K[2];       // directional symbols per axis (complex T)
     size_t D[2];       // derivative symbols per axis (T)
