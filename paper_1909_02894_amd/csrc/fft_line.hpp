@@ -170,12 +170,8 @@ __host__ __device__ inline int tw_pass_src(int n, int R, int e) {
     return -1;
 }
 
-// Largest LDS exchange buffer (bytes) that holds both spinor components of a
-// tile at once; larger tiles of threads carrying both exchange them one at a time.
-#ifndef DIRAC_LDS_BOTH_MAX
-#define DIRAC_LDS_BOTH_MAX (160 * 1024)
-#endif
-constexpr size_t kLdsBothMax = DIRAC_LDS_BOTH_MAX;
+constexpr size_t kLdsMax = 160 * 1024;         // LDS of a compute unit
+constexpr size_t kTwStageMax = 16 * 1024;      // largest twiddle table staged in LDS
 
 // Exchange of a 32-bit value with the partner lane (lane xor 32) of the same
 // wave, with gfx950's v_permlane32_swap (upper half of the first operand <->
@@ -222,20 +218,31 @@ struct LineFFT {
     // tile writes element (R j + s) L + l from lane (j, l): with 16 / R pads per
     // 16 elements, neighbouring j land L R + L elements apart, so the lanes of
     // one access cover distinct banks (one pad suffices for a single line).
-    // SEQ: when the layout of both components would not fit kLdsBothMax bytes, a
-    // thread carrying both (CPT = 2) exchanges them one after the other through
-    // a one-component buffer (twice the barriers, half the LDS; every value takes
-    // the same path, so results are bitwise the same).
+    // SEQ: a thread carrying both components (CPT = 2) exchanges them one after
+    // the other through a one-component buffer (twice the barriers, half the LDS,
+    // fewer registers; every value takes the same path, so results are bitwise the
+    // same).  Taken when both would not fit the LDS at all, and where the halved
+    // buffer lets more of the small workgroups (up to 256 threads) share a compute
+    // unit: tiles over 80 KB, and over 32 KB where the twiddles are staged beside
+    // them (us per launch, both at once / one after the other: flat FP32 2048 rows
+    // radix 8 41 / 35, columns radix 16 x 2 lines 61 / 40; FP64 1024 rows 27 / 25,
+    // curved 32 / 29, columns radix 8 x 2 lines 32 / 25).  Lines whose twiddles come
+    // from memory keep both at once up to 80 KB (curved FP64 2048 rows 100 / 181:
+    // the registers spill), and so do larger workgroups (FP32 4096 columns,
+    // radix 16 x 2 lines of 512 threads: 269 / 391, nothing more fits beside them).
     static constexpr int ROW_STRIDE = N + N / R;
     static constexpr int COL_PAD = (L == 1 || R >= 16) ? 1 : 16 / R;
     __host__ __device__ static constexpr int lds_elems(int ncomp) {
         return (NPASS > 1) ? (COLS ? ncomp * N * L + (ncomp * N * L / 16) * COL_PAD : L * ncomp * ROW_STRIDE) : 1;
     }
-    static constexpr bool SEQ = CPT == 2 && (lds_elems(2) * sizeof(cpx<T>) > kLdsBothMax ||
-                                              (lds_elems(2) * sizeof(cpx<T>) > kLdsBothMax / 2 && NT <= 256));
+    static constexpr size_t LDS_BOTH = lds_elems(2) * sizeof(cpx<T>);
+    static constexpr bool SEQ =
+        CPT == 2 && (LDS_BOTH > kLdsMax ||
+                     (NT <= 256 && (LDS_BOTH > kLdsMax / 2 ||
+                                    (LDS_BOTH > kLdsMax / 5 && N * sizeof(cpx<T>) <= kTwStageMax))));
     static constexpr int NCL = SEQ ? 1 : 2;        // components held in LDS at once
     static constexpr int LDS_ELEMS = lds_elems(NCL);
-    static_assert(LDS_ELEMS * sizeof(cpx<T>) <= 160 * 1024, "exchange buffer exceeds the LDS");
+    static_assert(LDS_ELEMS * sizeof(cpx<T>) <= kLdsMax, "exchange buffer exceeds the LDS");
     static_assert(CPT == 1 || CPT == 2, "components per thread");
     static_assert(N % R == 0, "R must divide N");
     static_assert(NPASS == 1 ? N == R : E >= 2, "schedule needs radix-R first and last passes");

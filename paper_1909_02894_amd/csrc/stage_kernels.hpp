@@ -150,7 +150,7 @@ __device__ __forceinline__ int xcd_tile(int b, int nb) {
 // so the per-pass twiddle reads do not sit on the critical path.
 template <typename T, int N>
 struct TwStage {
-    static constexpr bool ON = N * sizeof(cpx<T>) <= 16384;
+    static constexpr bool ON = N * sizeof(cpx<T>) <= kTwStageMax;
     static constexpr int ELEMS = ON ? N : 1;
 };
 

@@ -15,10 +15,10 @@ REG(512, 16, 8, 2)
 REGO(1024, 8, 4, 1)
 REG(1024, 8, 4, 2)
 REG(1024, 16, 4, 2)
+REG(2048, 16, 2, 2)
 REGO(2048, 8, 2, 2)
 REG(2048, 16, 4, 1)
 REG(2048, 16, 4, 2)
-REG(2048, 8, 4, 2)
 REGO(4096, 16, 2, 2)
 REG(4096, 16, 2, 1)
 REG(4096, 8, 2, 2)
