@@ -325,10 +325,15 @@ struct LineFFT {
     }
 
     // Exchange after pass PASS-1 and compute pass PASS (PASS >= 1).  PP: tw is
-    // the per-pass layout (else the plain table).
-    template <bool INV, bool PP, int PASS>
-    __device__ static __forceinline__ void pass(cpx<T> (&v)[CPT][R], cpx<T>* lds, const Coord& c,
+    // the per-pass layout (else the plain table).  NB: exchange buffers at lds,
+    // used in turn from number FIRST on; with two of them an exchange needs one
+    // barrier (a buffer is written again only after the barrier of the exchange
+    // in between, which every thread reaches after its reads of this one).
+    template <bool INV, bool PP, int PASS, int NB, int FIRST>
+    __device__ static __forceinline__ void pass(cpx<T> (&v)[CPT][R], cpx<T>* buf, const Coord& c,
                                                 const cpx<T>* __restrict__ tw) {
+        static_assert(NB == 1 || (NB == 2 && !SEQ), "one buffer, or two without SEQ");
+        cpx<T>* lds = buf + (NB == 2 ? ((FIRST + PASS - 1) & 1) * LDS_ELEMS : 0);
         constexpr int Rq = radix_of(PASS - 1), Nq = ns_of(PASS - 1);
         constexpr int Rp = radix_of(PASS), Ns = ns_of(PASS);
         // components [c0, c1) through the buffer: all at once, or one at a time (SEQ)
@@ -353,7 +358,7 @@ struct LineFFT {
                     for (int r = 0; r < Rp; ++r) v[cc][t * Rp + r] = lds[lidx(c.l, slot(c, cc), jj + r * (N / Rp))];
                 }
             }
-            __syncthreads();
+            if constexpr (NB == 1) __syncthreads();
         };
         if constexpr (SEQ) {
             exchange(0, 1);
@@ -375,19 +380,20 @@ struct LineFFT {
 #pragma unroll
             for (int cc = 0; cc < CPT; ++cc) dft<T, Rp, INV>(&v[cc][t * Rp]);
         }
-        if constexpr (PASS + 1 < NPASS) pass<INV, PP, PASS + 1>(v, lds, c, tw);
+        if constexpr (PASS + 1 < NPASS) pass<INV, PP, PASS + 1, NB, FIRST>(v, buf, c, tw);
     }
 
     // Transform the components this thread carries.  Entry: v[cc][r] = position
     // j + r P.  Exit: v[cc][s] = mode (forward) / position (inverse) j + s P.
     // tw: the plain table tw[m] = exp(-2 pi i m / N) (PP = false) or its
     // per-pass layout (PP = true); the inverse uses conjugates and is unnormalised.
-    template <bool INV, bool PP = false>
+    // With NB = 2 a following transform starts at buffer (FIRST + NPASS - 1) mod 2.
+    template <bool INV, bool PP = false, int NB = 1, int FIRST = 0>
     __device__ static __forceinline__ void fft(cpx<T> (&v)[CPT][R], cpx<T>* lds, const Coord& c,
                                                const cpx<T>* __restrict__ tw) {
 #pragma unroll
         for (int cc = 0; cc < CPT; ++cc) dft<T, R, INV>(v[cc]);
-        if constexpr (NPASS > 1) pass<INV, PP, 1>(v, lds, c, tw);
+        if constexpr (NPASS > 1) pass<INV, PP, 1, NB, FIRST>(v, lds, c, tw);
     }
 };
 

@@ -154,16 +154,27 @@ struct TwStage {
     static constexpr int ELEMS = ON ? N : 1;
 };
 
+// Exchange buffers of a single solve's direction kernel: two (one barrier per
+// exchange instead of two) for the tiles of one component per lane, whose solves
+// are small and bound by latency, where at least three workgroups still fit a
+// compute unit.  us per step, one buffer / two: curved FP64 512^2 17.6 / 17.0,
+// FP32 12.9 / 12.5; FP64 128^2 9.0 / 8.6.
+template <typename T, int N, int R, int L, bool COLS, int CPT>
+constexpr int stage_buffers() {
+    using F = LineFFT<T, N, R, L, COLS, CPT>;
+    return CPT == 1 && F::NPASS > 1 && 3 * (2 * F::LDS_ELEMS + TwStage<T, N>::ELEMS) * sizeof(cpx<T>) <= kLdsMax ? 2 : 1;
+}
+
 // MODE 0: flat, no absorbing layer (b = 1: psi <- Xi; E uniform diagonal)
 // MODE 1: flat with layer (b = 1/S along the line; E uniform diagonal)
 // MODE 2: curved (b = a(x) [/S]; E from the per-point table)
 // One tile (L lines) of a direction stage, executed by F::NT threads.  lds and
-// twl are the workgroup's exchange buffer (F::LDS_ELEMS) and twiddle stage
+// twl are the workgroup's NB exchange buffers (F::LDS_ELEMS each) and twiddle stage
 // (TwStage::ELEMS).  Every per-line operation depends on (T, N, R, MODE) only:
 // the 2x2 mixes are written per output component as (own, other) expressions
 // that are the same whether the other component sits in the same thread
 // (CPT = 2) or in the partner lane (CPT = 1), so results do not depend on L or CPT.
-template <typename T, int N, int R, int L, bool COLS, int MODE, int CPT>
+template <typename T, int N, int R, int L, bool COLS, int MODE, int CPT, int NB = 1>
 __device__ __forceinline__ void stage_tile(const StageParams<T>& p, int tile, cpx<T>* lds, cpx<T>* twl) {
     using F = LineFFT<T, N, R, L, COLS, CPT>;
     using TS = TwStage<T, N>;
@@ -291,7 +302,7 @@ __device__ __forceinline__ void stage_tile(const StageParams<T>& p, int tile, cp
             for (int r = 0; r < R; ++r) old[cc][r] = v[cc][r];
     }
 
-    F::template fft<false, true>(v, lds, c, tw);
+    F::template fft<false, true, NB>(v, lds, c, tw);
     mix(v, [&](cpx<T> own, cpx<T> other, int comp, int s) {
         cpx<T> k;
         if constexpr (PF) k = kk[s];
@@ -302,7 +313,7 @@ __device__ __forceinline__ void stage_tile(const StageParams<T>& p, int tile, cp
             return scal(k.re, own) - scal(comp ? -k.im : k.im, other);
         }
     });
-    F::template fft<true, true>(v, lds, c, tw);
+    F::template fft<true, true, NB, (F::NPASS - 1) % 2>(v, lds, c, tw);
 
     if constexpr (BLEND) {
         if constexpr (REREAD) {
@@ -347,9 +358,10 @@ __device__ __forceinline__ void stage_tile(const StageParams<T>& p, int tile, cp
 template <typename T, int N, int R, int L, bool COLS, int MODE, int CPT>
 __global__ void __launch_bounds__((CPT == 1 ? 2 : 1) * (N / R) * L)
 stage_kernel(StageParams<T> p) {
-    __shared__ cpx<T> lds[LineFFT<T, N, R, L, COLS, CPT>::LDS_ELEMS];
+    constexpr int NB = stage_buffers<T, N, R, L, COLS, CPT>();
+    __shared__ cpx<T> lds[NB * LineFFT<T, N, R, L, COLS, CPT>::LDS_ELEMS];
     __shared__ cpx<T> twl[TwStage<T, N>::ELEMS];
-    stage_tile<T, N, R, L, COLS, MODE, CPT>(p, xcd_tile(blockIdx.x, gridDim.x), lds, twl);
+    stage_tile<T, N, R, L, COLS, MODE, CPT, NB>(p, xcd_tile(blockIdx.x, gridDim.x), lds, twl);
 }
 
 // Deterministic workgroup sum of NV doubles per thread into out[0..NV).
