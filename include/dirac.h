@@ -295,10 +295,10 @@ dirac_status dirac_set_schedule(dirac_solver* s, int32_t direction, const dirac_
 /* State stores of the direction kernels, a bit mask: bit 0 for the x kernel,
  * bit 1 for the y kernel; a set bit selects device-scope write-through stores,
  * which send each line to memory at once instead of leaving it dirty in the
- * XCD's L2 until the kernel ends (0 = ordinary stores, the default).
- * Write-through pays on some small grids whose kernels are latency-bound and
- * loses on large streaming ones; dirac_autotune measures both per direction
- * and keeps the faster.  Results are bitwise the same either way.  Every form
+ * XCD's L2 until the kernel ends (0 = ordinary stores).  Write-through pays on
+ * small grids whose kernels are latency-bound and loses on large streaming ones:
+ * the default goes by the state's size (up to 16 MB in FP64, 32 MB in FP32);
+ * dirac_autotune measures both per direction and keeps the faster.  Results are bitwise the same either way.  Every form
  * of Scheme II's directional step (not Scheme I); write-through for the y
  * kernel only with n2 <= 1024 (else DIRAC_E_ARG). */
 dirac_status dirac_set_store_mode(dirac_solver* s, int32_t write_through);

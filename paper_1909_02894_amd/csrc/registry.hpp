@@ -16,6 +16,7 @@ struct KernelEntry {
     int nthreads;   // workgroup size
     const void* stage_fn[3];   // by mode: 0 flat, 1 flat + layer, 2 curved
     const void* obs_fn;
+    int from_lines[2];         // [flat, blended]: default schedule from this many lines (negative: never)
 };
 
 std::vector<KernelEntry>& kernel_registry();
@@ -30,16 +31,21 @@ struct Registrar {
 // float), DIRAC_PREC (0/1), DIRAC_COLS (false/true), DIRAC_DIR (0/1).
 #define DIRAC_CAT2(a, b) a##b
 #define DIRAC_CAT(a, b) DIRAC_CAT2(a, b)
-#define DIRAC_REG_IMPL(N, R, L, CPT, OBS)                                                             \
+#define DIRAC_REG_IMPL(N, R, L, CPT, OBS, FLAT, BLEND)                                                \
     static ::dirac::Registrar DIRAC_CAT(reg_, __LINE__)(::dirac::KernelEntry{                        \
         DIRAC_PREC, N, DIRAC_DIR, R, L, CPT,                                                          \
         ::dirac::LineFFT<DIRAC_T, N, R, L, DIRAC_COLS, CPT>::NT,                                       \
         {reinterpret_cast<const void*>(&::dirac::stage_kernel<DIRAC_T, N, R, L, DIRAC_COLS, 0, CPT>), \
          reinterpret_cast<const void*>(&::dirac::stage_kernel<DIRAC_T, N, R, L, DIRAC_COLS, 1, CPT>), \
          reinterpret_cast<const void*>(&::dirac::stage_kernel<DIRAC_T, N, R, L, DIRAC_COLS, 2, CPT>)},\
-        OBS});
-// REG: a direction-kernel schedule.  REGO: the same plus the observable kernel
-// with that schedule (one per precision, n and direction).
-#define REG(N, R, L, CPT) DIRAC_REG_IMPL(N, R, L, CPT, nullptr)
-#define REGO(N, R, L, CPT) \
-    DIRAC_REG_IMPL(N, R, L, CPT, reinterpret_cast<const void*>(&::dirac::obs_kernel<DIRAC_T, N, R, L, DIRAC_COLS, CPT>))
+        OBS, {FLAT, BLEND}});
+// REG: a direction-kernel schedule.  REGD: one that is the default of flat grids
+// (FLAT) and of grids with a layer or a metric (BLEND) that have at least that
+// many lines, up to the next threshold (a negative number: never).  REGO / REGOD:
+// the same plus the observable kernel with that schedule (one per precision, n
+// and direction).
+#define REG(N, R, L, CPT) DIRAC_REG_IMPL(N, R, L, CPT, nullptr, -1, -1)
+#define REGD(N, R, L, CPT, FLAT, BLEND) DIRAC_REG_IMPL(N, R, L, CPT, nullptr, FLAT, BLEND)
+#define DIRAC_OBS(N, R, L, CPT) reinterpret_cast<const void*>(&::dirac::obs_kernel<DIRAC_T, N, R, L, DIRAC_COLS, CPT>)
+#define REGO(N, R, L, CPT) DIRAC_REG_IMPL(N, R, L, CPT, DIRAC_OBS(N, R, L, CPT), -1, -1)
+#define REGOD(N, R, L, CPT, FLAT, BLEND) DIRAC_REG_IMPL(N, R, L, CPT, DIRAC_OBS(N, R, L, CPT), FLAT, BLEND)

@@ -239,10 +239,17 @@ const KernelEntry* find_entry(int prec, int n, int dir, const dirac_schedule& s)
             return &e;
     return nullptr;
 }
-const KernelEntry* default_entry(int prec, int n, int dir) {
-    for (const auto& e : kernel_registry())
-        if (e.prec == prec && e.n == n && e.dir == dir) return &e;
-    return nullptr;
+// Default schedule of `lines` lines of n points: the entry with the largest
+// threshold not above it, for flat or blended (layer or metric) kernels.
+const KernelEntry* default_entry(int prec, int n, int dir, int lines, bool blended) {
+    const KernelEntry* best = nullptr;
+    for (const auto& e : kernel_registry()) {
+        const int from = e.from_lines[blended ? 1 : 0];
+        if (e.prec == prec && e.n == n && e.dir == dir && from >= 0 && from <= lines &&
+            (!best || from > best->from_lines[blended ? 1 : 0]))
+            best = &e;
+    }
+    return best;
 }
 const KernelEntry* obs_entry(int prec, int n, int dir) {
     for (const auto& e : kernel_registry())
@@ -273,11 +280,23 @@ int tune_mode(const dirac_solver* s) {
 bool store_wt_compiled(const dirac_solver* s, int dir) { return dir == 0 || s->g.n2 <= kStoreWtMaxColN; }
 
 // Store mode the autotuner measured fastest for this direction and shape, else
-// ordinary stores.
+// by size.
 bool pick_store_mode(int prec, int n, int dir, int other, int mode) {
-    std::lock_guard<std::mutex> lk(tune_mutex());
-    auto it = tune_cache().find(TuneKey{prec, n, dir, other, mode});
-    return it != tune_cache().end() && it->second.wt != 0;
+    {
+        std::lock_guard<std::mutex> lk(tune_mutex());
+        auto it = tune_cache().find(TuneKey{prec, n, dir, other, mode});
+        if (it != tune_cache().end()) return it->second.wt != 0;
+    }
+    // Not tuned: write-through on the grids whose kernels otherwise end waiting
+    // for the write-back of their stores, i.e. states up to 16 MB (32 MB in
+    // FP32).  us per step, ordinary / written through, default schedules: curved
+    // FP64 512^2 24.8 / 17.4, 1024 x 256 25.7 / 17.0, FP32 1024^2 34.5 / 27.3,
+    // 4096 x 512 54.1 / 49.7; larger ones gain little or lose: curved FP64 1024^2 54.1 / 64.1,
+    // 2048 x 512 48.9 / 51.8.  Columns longer than 256 points of a
+    // grid narrower than 256 are few, and written through in pieces of a cache
+    // line: 64 x 512 FP64 9.6 / 10.2.
+    const size_t bytes = (size_t)n * other * 4 * (prec == DIRAC_FP32 ? 4 : 8);
+    return bytes <= size_t(prec == DIRAC_FP32 ? 32 : 16) << 20 && (dir == 0 || n <= 256 || other >= 256);
 }
 
 const KernelEntry* pick_entry(int prec, int n, int dir, int other, int mode) {
@@ -289,7 +308,7 @@ const KernelEntry* pick_entry(int prec, int n, int dir, int other, int mode) {
             if (const KernelEntry* e = find_entry(prec, n, dir, sc)) return e;
         }
     }
-    return default_entry(prec, n, dir);
+    return default_entry(prec, n, dir, other, (mode & 3) != 0);
 }
 
 // ---------------------------------------------------------------- launches
@@ -624,7 +643,7 @@ dirac_status dirac_create_solver(const dirac_grid* g, const dirac_metric* m, con
         return fail(DIRAC_E_SIZE, "device buffer of %zu bytes < footprint %zu", bytes, lay.total);
     for (int dir = 0; dir < 2; ++dir) {
         const int n = dir == 0 ? g->n1 : g->n2;
-        if (!default_entry(prec, n, dir) || !obs_entry(prec, n, dir))
+        if (!obs_entry(prec, n, dir))
             return fail(DIRAC_E_SIZE, "no compiled kernel for n = %d (precision %d, direction %d)", n, prec, dir);
     }
     // Check the pointer is device memory of the current device.

@@ -36,10 +36,27 @@ __device__ double pml_inv_s(int k, int n, double a, int width, int type, double 
 template <typename T>
 __device__ void put(void* base, size_t i, double v) { static_cast<T*>(base)[i] = (T)v; }
 
+// Row 0 of the grid writes the axis tables, rows 1..3 the per-pass twiddle
+// layouts (side by side: one after the other in a thread, creation took 57 us longer).
 __global__ void setup_axis_kernel(SetupAxisParams p) {
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= p.n) return;
     const int n = p.n;
+    if (blockIdx.y > 0) {
+        const int i = blockIdx.y - 1;
+        if (!p.twp[i]) return;
+        const int m = tw_pass_src(n, 4 << i, k);
+        double s = 0.0, c = 1.0;                        // the same FP64 values as the plain table
+        if (m >= 0) sincospi(2.0 * m / n, &s, &c);
+        if (p.fp32) {
+            put<float>(p.twp[i], 2 * k, c);
+            put<float>(p.twp[i], 2 * k + 1, -s);
+        } else {
+            put<double>(p.twp[i], 2 * k, c);
+            put<double>(p.twp[i], 2 * k + 1, -s);
+        }
+        return;
+    }
     const double invs = pml_inv_s(k, n, p.a, p.pml_width, p.pml_type, p.sigma0, p.ctheta);
     const int pp = k < n / 2 ? k : k - n;               // Nyquist keeps p = -n/2
     const double xi = pp * M_PI / p.a;
@@ -63,20 +80,6 @@ __global__ void setup_axis_kernel(SetupAxisParams p) {
         put<double>(p.D, k, xi * inv_n);
         put<double>(p.tw, 2 * k, tc);
         put<double>(p.tw, 2 * k + 1, -ts);
-    }
-    // entry k of the per-pass layouts: the same FP64 values as the plain table
-    for (int i = 0; i < 3; ++i) {
-        if (!p.twp[i]) continue;
-        const int m = tw_pass_src(n, 4 << i, k);
-        double s = 0.0, c = 1.0;
-        if (m >= 0) sincospi(2.0 * m / n, &s, &c);
-        if (p.fp32) {
-            put<float>(p.twp[i], 2 * k, c);
-            put<float>(p.twp[i], 2 * k + 1, -s);
-        } else {
-            put<double>(p.twp[i], 2 * k, c);
-            put<double>(p.twp[i], 2 * k + 1, -s);
-        }
     }
 }
 
@@ -333,7 +336,7 @@ hipError_t launch_transpose(const void* in, void* out, int n1, int n2, int elem,
 }
 
 hipError_t launch_setup_axis(const SetupAxisParams& p, hipStream_t s) {
-    hipLaunchKernelGGL(setup_axis_kernel, dim3((p.n + 255) / 256), dim3(256), 0, s, p);
+    hipLaunchKernelGGL(setup_axis_kernel, dim3((p.n + 255) / 256, p.twp[0] ? 4 : 1), dim3(256), 0, s, p);
     return hipGetLastError();
 }
 hipError_t launch_setup_points(const SetupPointParams& p, double* fold_out, hipStream_t s) {
