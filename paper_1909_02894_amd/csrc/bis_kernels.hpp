@@ -7,9 +7,8 @@
 // i.e. the blend of eq. (second_scheme) plus the difference between the exact
 // transport d_t psi = -c b sigma_i d_i psi and the blend at second order in dt.
 // Three inverse transforms share the forward one; Step 1 / Step 5 are fused as
-// in the plain direction kernel.  One schedule per size: radix 4, both
-// components in a thread, 256-thread workgroups (n / 4 threads per line up to
-// n = 2048).
+// in the plain direction kernel.  One schedule per size, radix 4 (bis_cpt,
+// bis_lines), up to n = 2048.
 #pragma once
 #include "stage_kernels.hpp"
 
@@ -26,31 +25,38 @@ struct BisParams {
 
 struct BisEntry {
     int prec, n, dir, lines, nthreads;
+    int from_lines;        // for this many lines and more
     const void* fn[2];     // [0] flat with layer, [1] curved
 };
 
-// Radix 4; one row or two columns per workgroup (row segments of two points)
-// from 64-thread lines, so that a 512-point grid gives every SIMD a wave; at
-// least 64 threads per workgroup.
+// Shape of the kernel of n-point lines.  Up to 512 points one spinor component per
+// lane (twice the waves of the two-component form, whose single wave per SIMD was
+// bound by its own chain) and as few lines per workgroup as whole waves allow, two
+// of 512-point columns; the inverse transforms run side by side, sharing barriers
+// and twiddle reads.  Curved 512^2: FP64 35.4 -> 26.1 us per step, FP32 22.6 -> 18.5.
+// Longer lines, and 1024 and more columns of 512 points: both components per
+// thread, the inverse transforms one after the other (three exchange buffers do
+// not fit, or leave one workgroup per compute unit: FP64 2048 x 512 111 against 121).
 constexpr int kBisRadix = 4;
-__host__ __device__ constexpr int bis_lines(int n, bool cols) {
-    return (n / kBisRadix) >= 256 ? 1
-           : (n / kBisRadix) >= 64 ? (cols ? 2 : 1)
-           : (cols && 64 / (n / kBisRadix) < 2 ? 2 : 64 / (n / kBisRadix));
+__host__ __device__ constexpr int bis_cpt(int n) { return n <= 512 ? 1 : 2; }
+__host__ __device__ constexpr int bis_lines(int n) { return n / kBisRadix < 32 ? 32 / (n / kBisRadix) : 1; }
+__host__ __device__ constexpr int bis_threads(int n, int lines, int cpt) {
+    return (n / kBisRadix) * lines * (cpt == 1 ? 2 : 1);
 }
-__host__ __device__ constexpr int bis_threads(int n, bool cols) { return (n / kBisRadix) * bis_lines(n, cols); }
 
-const BisEntry* bis_entry(int prec, int n, int dir);
+const BisEntry* bis_entry(int prec, int n, int dir, int nlines);
 
 // MODE 1: flat with layer (b = 1/S, b' = 0, uniform diagonal E); MODE 2: curved.
-template <typename T, int N, bool COLS, int MODE>
-__global__ void __launch_bounds__(bis_threads(N, COLS)) bis_stage_kernel(BisParams<T> bp) {
-    constexpr int R = kBisRadix, L = bis_lines(N, COLS);
-    using F = LineFFT<T, N, R, L, COLS, 2>;
+template <typename T, int N, int L, int CPT, bool COLS, int MODE>
+__global__ void __launch_bounds__(bis_threads(N, L, CPT)) bis_stage_kernel(BisParams<T> bp) {
+    constexpr int R = kBisRadix;
+    using F = LineFFT<T, N, R, L, COLS, CPT, false>;
     using TS = TwStage<T, N>;
     constexpr int P = F::P;
     constexpr int dir = COLS ? 1 : 0;
-    __shared__ cpx<T> lds[F::LDS_ELEMS];
+    constexpr int NV = MODE == 2 ? 3 : 2;              // inverse transforms
+    constexpr bool BATCH = CPT == 1;
+    __shared__ cpx<T> lds[(BATCH ? NV : 1) * F::LDS_ELEMS];
     __shared__ cpx<T> twl[TS::ELEMS];
     const StageParams<T>& p = bp.s;
     const typename F::Coord c = F::coord(threadIdx.x);
@@ -62,10 +68,26 @@ __global__ void __launch_bounds__(bis_threads(N, COLS)) bis_stage_kernel(BisPara
         return COLS ? (uint32_t)pos * n1 + ln : (uint32_t)ln * n1 + pos;
     };
 
-    // every global load of the tile goes out before the first wait
-    cpx<T> v[2][R];
+    // t[cc][r] <- f(own, other, component, r) of a, for every carried component
+    auto mix = [&](const cpx<T> (*a)[R], cpx<T> (*t)[R], auto&& f) {
 #pragma unroll
-    for (int r = 0; r < R; ++r) load_point(p.psi, gidx(lline, c.j + r * P), v[0][r], v[1][r]);
+        for (int r = 0; r < R; ++r) {
+            if constexpr (CPT == 1) {
+                t[0][r] = f(a[0][r], partner(a[0][r]), c.comp, r);
+            } else {
+                const cpx<T> a0 = a[0][r], a1 = a[1][r];
+                t[0][r] = f(a0, a1, 0, r);
+                t[1][r] = f(a1, a0, 1, r);
+            }
+        }
+    };
+    // every global load of the tile goes out before the first wait
+    cpx<T> v[CPT][R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        if constexpr (CPT == 1) v[0][r] = load_comp(p.psi, gidx(lline, c.j + r * P), c.comp);
+        else load_point(p.psi, gidx(lline, c.j + r * P), v[0][r], v[1][r]);
+    }
     // Step 1 / Step 5: row comp of E = [[e0, e1], [conj e1, conj e0]];
     // direction-x launches always open with Step 1 and load E up front
     constexpr bool PRELOAD_E = MODE == 2 && !COLS;
@@ -103,24 +125,14 @@ __global__ void __launch_bounds__(bis_threads(N, COLS)) bis_stage_kernel(BisPara
         tw = twl;
     }
     auto applyE = [&](int times) {
-        if constexpr (MODE == 2) {
-            for (int t = 0; t < times; ++t) {
-#pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    const cpx<T> u = v[0][r], w = v[1][r];
-                    v[0][r] = cmul(e0[r], u) + cmul(e1[r], w);
-                    v[1][r] = cmul(cpx<T>{e0[r].re, -e0[r].im}, w) + cmul(cpx<T>{e1[r].re, -e1[r].im}, u);
-                }
-            }
-        } else {                               // uniform diag(e0u, conj e0u)
-            for (int t = 0; t < times; ++t) {
-#pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    v[0][r] = cmul(p.e0u, v[0][r]);
-                    v[1][r] = cmul(cpx<T>{p.e0u.re, -p.e0u.im}, v[1][r]);
-                }
-            }
-        }
+        for (int t = 0; t < times; ++t)
+            mix(v, v, [&](cpx<T> own, cpx<T> other, int comp, int r) {
+                const T sg = comp ? T(-1) : T(1);
+                if constexpr (MODE == 2)
+                    return cmul(cpx<T>{e0[r].re, sg * e0[r].im}, own) + cmul(cpx<T>{e1[r].re, sg * e1[r].im}, other);
+                else                               // uniform diag(e0u, conj e0u)
+                    return cmul(cpx<T>{p.e0u.re, sg * p.e0u.im}, own);
+            });
     };
     if constexpr (PRELOAD_E) {
         applyE(1);                             // e_pre is 1 or 2 here
@@ -129,62 +141,76 @@ __global__ void __launch_bounds__(bis_threads(N, COLS)) bis_stage_kernel(BisPara
         loadE();
         applyE(p.e_pre);
     }
-    cpx<T> old[2][R];
+    cpx<T> old[CPT][R];
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        old[0][r] = v[0][r];
-        old[1][r] = v[1][r];
-    }
+    for (int cc = 0; cc < CPT; ++cc)
+#pragma unroll
+        for (int r = 0; r < R; ++r) old[cc][r] = v[cc][r];
 
     F::template fft<false, true>(v, lds, c, tw);
-    cpx<T> acc[2][R], t[2][R];
-    // b (1 - b) (c dt)^2 / 2 * F^-1[xi^2 psi_hat]
+    // the spectra of the inverse transforms: K psi_hat, xi^2 psi_hat, i xi psi_hat
+    auto symK = [&](cpx<T> (*t)[R]) {
+        mix(v, t, [&](cpx<T> own, cpx<T> other, int comp, int s) {
+            const cpx<T> k = ksym[s];
+            if constexpr (!COLS) return scal(k.re, own) + mul_mi(scal(k.im, other));  // K_x = cos I - i sin sigma_x
+            else return scal(k.re, own) - scal(comp ? -k.im : k.im, other);           // K_y = [[cos, -sin], [sin, cos]]
+        });
+    };
+    auto sym2 = [&](cpx<T> (*t)[R]) {
 #pragma unroll
-    for (int s = 0; s < R; ++s) {
-        const T d = dsym[s];
-        const T w2 = bp.n * d * d;
-        t[0][s] = scal(w2, v[0][s]);
-        t[1][s] = scal(w2, v[1][s]);
-    }
-    F::template fft<true, true>(t, lds, c, tw);
+        for (int cc = 0; cc < CPT; ++cc)
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        acc[0][r] = scal(k2[r], t[0][r]);
-        acc[1][r] = scal(k2[r], t[1][r]);
-    }
-    if constexpr (MODE == 2) {
-        // + b b' (c dt)^2 / 2 * F^-1[i xi psi_hat]
+            for (int s = 0; s < R; ++s) t[cc][s] = scal(bp.n * dsym[s] * dsym[s], v[cc][s]);
+    };
+    auto sym1 = [&](cpx<T> (*t)[R]) {
 #pragma unroll
-        for (int s = 0; s < R; ++s) {
-            const T d = dsym[s];
-            t[0][s] = mul_i(scal(d, v[0][s]));
-            t[1][s] = mul_i(scal(d, v[1][s]));
-        }
+        for (int cc = 0; cc < CPT; ++cc)
+#pragma unroll
+            for (int s = 0; s < R; ++s) t[cc][s] = mul_i(scal(dsym[s], v[cc][s]));
+    };
+    cpx<T> acc[CPT][R];
+    // (c dt)^2 / 2 (b (1 - b) F^-1[xi^2 psi_hat] + b b' F^-1[i xi psi_hat])
+    auto add2 = [&](const cpx<T> (*t)[R]) {
+#pragma unroll
+        for (int cc = 0; cc < CPT; ++cc)
+#pragma unroll
+            for (int r = 0; r < R; ++r) acc[cc][r] = scal(k2[r], t[cc][r]);
+    };
+    auto add1 = [&](const cpx<T> (*t)[R]) {
+#pragma unroll
+        for (int cc = 0; cc < CPT; ++cc)
+#pragma unroll
+            for (int r = 0; r < R; ++r) acc[cc][r] = acc[cc][r] + scal(k1[r], t[cc][r]);
+    };
+    if constexpr (BATCH) {
+        cpx<T> t[NV * CPT][R];
+        symK(t);
+        sym2(t + CPT);
+        if constexpr (MODE == 2) sym1(t + 2 * CPT);
+        F::template fft<true, true, 1, 0, NV>(t, lds, c, tw);
+        add2(t + CPT);
+        if constexpr (MODE == 2) add1(t + 2 * CPT);
+#pragma unroll
+        for (int cc = 0; cc < CPT; ++cc)
+#pragma unroll
+            for (int r = 0; r < R; ++r) v[cc][r] = t[cc][r];
+    } else {
+        cpx<T> t[CPT][R];
+        sym2(t);
         F::template fft<true, true>(t, lds, c, tw);
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            acc[0][r] = acc[0][r] + scal(k1[r], t[0][r]);
-            acc[1][r] = acc[1][r] + scal(k1[r], t[1][r]);
+        add2(t);
+        if constexpr (MODE == 2) {
+            sym1(t);
+            F::template fft<true, true>(t, lds, c, tw);
+            add1(t);
         }
+        symK(v);
+        F::template fft<true, true>(v, lds, c, tw);
     }
-    // Xi = F^-1[K psi_hat]
-#pragma unroll
-    for (int s = 0; s < R; ++s) {
-        const cpx<T> k = ksym[s];
-        const cpx<T> a0 = v[0][s], a1 = v[1][s];
-        if constexpr (!COLS) {                 // K_x = cos I - i sin sigma_x
-            v[0][s] = scal(k.re, a0) + mul_mi(scal(k.im, a1));
-            v[1][s] = scal(k.re, a1) + mul_mi(scal(k.im, a0));
-        } else {                               // K_y = [[cos, -sin], [sin, cos]]
-            v[0][s] = scal(k.re, a0) - scal(k.im, a1);
-            v[1][s] = scal(k.re, a1) + scal(k.im, a0);
-        }
-    }
-    F::template fft<true, true>(v, lds, c, tw);
 #pragma unroll
     for (int r = 0; r < R; ++r) {
 #pragma unroll
-        for (int cc = 0; cc < 2; ++cc)
+        for (int cc = 0; cc < CPT; ++cc)
             v[cc][r] = scal(b[r], v[cc][r]) + scal(T(1) - b[r], old[cc][r]) + acc[cc][r];
     }
     if (p.e_post) {
@@ -192,12 +218,17 @@ __global__ void __launch_bounds__(bis_threads(N, COLS)) bis_stage_kernel(BisPara
         applyE(1);
     }
     if (!valid) return;
-    if ((!COLS || N <= kStoreWtMaxColN) && p.wt) {     // write-through (as in stage_tile)
+    const bool wt = (!COLS || N <= kStoreWtMaxColN) && p.wt;       // write-through (as in stage_tile)
 #pragma unroll
-        for (int r = 0; r < R; ++r) store_point<T, true>(p.psi, gidx(line, c.j + r * P), v[0][r], v[1][r]);
-    } else {
-#pragma unroll
-        for (int r = 0; r < R; ++r) store_point(p.psi, gidx(line, c.j + r * P), v[0][r], v[1][r]);
+    for (int r = 0; r < R; ++r) {
+        const uint32_t q = gidx(line, c.j + r * P);
+        if constexpr (CPT == 1) {
+            if (wt) store_comp<T, true>(p.psi, q, c.comp, v[0][r]);
+            else store_comp(p.psi, q, c.comp, v[0][r]);
+        } else {
+            if (wt) store_point<T, true>(p.psi, q, v[0][r], v[1][r]);
+            else store_point(p.psi, q, v[0][r], v[1][r]);
+        }
     }
 }
 

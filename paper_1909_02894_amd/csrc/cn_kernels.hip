@@ -48,7 +48,7 @@ template <int N, bool COLS, bool M2 = false>
 struct CnTile {
     static constexpr int R = M2 ? cn2_radix(N) : cn_radix(N, COLS), L = M2 ? cn2_lines(N) : cn_lines(N, COLS);
     static constexpr int CPT = M2 ? kCn2Cpt : cn_cpt(COLS);
-    using F = LineFFT<double, N, R, L, COLS, CPT>;
+    using F = LineFFT<double, N, R, L, COLS, CPT, false>;
     static constexpr int NT = F::NT;
     static constexpr int LDS = F::LDS_ELEMS;
     static constexpr int TW = TwStage<double, N>::ELEMS;

@@ -98,7 +98,7 @@ __global__ void __launch_bounds__(d3_threads<T>(N)) d3_stage_kernel(D3Params<T> 
     constexpr int R = d3_radix<T>(N), L = d3_lines<T>(N);
     constexpr bool COLS = DIR != 0;
     constexpr bool BLEND = MODE != 0;
-    using F = LineFFT<T, N, R, L, COLS, 2>;
+    using F = LineFFT<T, N, R, L, COLS, 2, false>;
     using TS = TwStage<T, N>;
     constexpr int P = F::P;
     __shared__ cpx<T> lds[F::LDS_ELEMS];

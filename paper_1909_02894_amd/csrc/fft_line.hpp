@@ -203,7 +203,9 @@ __device__ __forceinline__ cpx<T> partner(cpx<T> v) { return {partner(v.re), par
 // 2x2 mixes (half-step exponential, directional symbol) exchange them with one
 // permlane swap (NT = 2 P L threads, half the registers per thread).
 // A line of N points is held by P = N / R logical threads.
-template <typename T, int N, int R, int L, bool COLS, int CPT>
+// TIGHT: the plain direction kernels' rule for exchanging one component at a time
+// (SEQ below); kernels with more state per thread than those keep both at once.
+template <typename T, int N, int R, int L, bool COLS, int CPT, bool TIGHT = true>
 struct LineFFT {
     static constexpr int P = N / R;
     static constexpr int NTL = P * L;
@@ -230,6 +232,8 @@ struct LineFFT {
     // from memory keep both at once up to 80 KB (curved FP64 2048 rows 100 / 181:
     // the registers spill), and so do larger workgroups (FP32 4096 columns,
     // radix 16 x 2 lines of 512 threads: 269 / 391, nothing more fits beside them).
+    // Not TIGHT: flat FP32 3-D 256 x 256 x 128 300 / 319 us per step, corrected
+    // second-order FP64 1024^2 87.5 / 89.6.
     static constexpr int ROW_STRIDE = N + N / R;
     static constexpr int COL_PAD = (L == 1 || R >= 16) ? 1 : 16 / R;
     __host__ __device__ static constexpr int lds_elems(int ncomp) {
@@ -239,7 +243,7 @@ struct LineFFT {
     static constexpr bool SEQ =
         CPT == 2 && (LDS_BOTH > kLdsMax ||
                      (NT <= 256 && (LDS_BOTH > kLdsMax / 2 ||
-                                    (LDS_BOTH > kLdsMax / 5 && N * sizeof(cpx<T>) <= kTwStageMax))));
+                                    (TIGHT && LDS_BOTH > kLdsMax / 5 && N * sizeof(cpx<T>) <= kTwStageMax))));
     static constexpr int NCL = SEQ ? 1 : 2;        // components held in LDS at once
     static constexpr int LDS_ELEMS = lds_elems(NCL);
     static_assert(LDS_ELEMS * sizeof(cpx<T>) <= kLdsMax, "exchange buffer exceeds the LDS");
@@ -325,15 +329,17 @@ struct LineFFT {
     }
 
     // Exchange after pass PASS-1 and compute pass PASS (PASS >= 1).  PP: tw is
-    // the per-pass layout (else the plain table).  NB: exchange buffers at lds,
-    // used in turn from number FIRST on; with two of them an exchange needs one
+    // the per-pass layout (else the plain table).  NV: vectors transformed side by
+    // side (v holds NV x CPT rows of R), sharing the barriers and twiddle reads.
+    // NB: exchange buffers (of NV x LDS_ELEMS) at buf, used in turn from number
+    // FIRST on; with two of them an exchange needs one
     // barrier (a buffer is written again only after the barrier of the exchange
     // in between, which every thread reaches after its reads of this one).
-    template <bool INV, bool PP, int PASS, int NB, int FIRST>
-    __device__ static __forceinline__ void pass(cpx<T> (&v)[CPT][R], cpx<T>* buf, const Coord& c,
+    template <bool INV, bool PP, int PASS, int NB, int FIRST, int NV>
+    __device__ static __forceinline__ void pass(cpx<T> (*v)[R], cpx<T>* buf, const Coord& c,
                                                 const cpx<T>* __restrict__ tw) {
-        static_assert(NB == 1 || (NB == 2 && !SEQ), "one buffer, or two without SEQ");
-        cpx<T>* lds = buf + (NB == 2 ? ((FIRST + PASS - 1) & 1) * LDS_ELEMS : 0);
+        static_assert((NB == 1 && NV == 1) || (NB <= 2 && !SEQ), "several buffers or vectors without SEQ only");
+        cpx<T>* lds = buf + (NB == 2 ? ((FIRST + PASS - 1) & 1) * NV * LDS_ELEMS : 0);
         constexpr int Rq = radix_of(PASS - 1), Nq = ns_of(PASS - 1);
         constexpr int Rp = radix_of(PASS), Ns = ns_of(PASS);
         // components [c0, c1) through the buffer: all at once, or one at a time (SEQ)
@@ -345,7 +351,8 @@ struct LineFFT {
                     const int jj = c.j + t * P;
                     const int base = (jj / Nq) * Nq * Rq + (jj % Nq);
 #pragma unroll
-                    for (int s = 0; s < Rq; ++s) lds[lidx(c.l, slot(c, cc), base + s * Nq)] = v[cc][t * Rq + s];
+                    for (int s = 0; s < Rq; ++s)
+                        lds[(cc / CPT) * LDS_ELEMS + lidx(c.l, slot(c, cc % CPT), base + s * Nq)] = v[cc][t * Rq + s];
                 }
             }
             __syncthreads();
@@ -355,7 +362,8 @@ struct LineFFT {
                 for (int t = 0; t < R / Rp; ++t) {
                     const int jj = c.j + t * P;
 #pragma unroll
-                    for (int r = 0; r < Rp; ++r) v[cc][t * Rp + r] = lds[lidx(c.l, slot(c, cc), jj + r * (N / Rp))];
+                    for (int r = 0; r < Rp; ++r)
+                        v[cc][t * Rp + r] = lds[(cc / CPT) * LDS_ELEMS + lidx(c.l, slot(c, cc % CPT), jj + r * (N / Rp))];
                 }
             }
             if constexpr (NB == 1) __syncthreads();
@@ -364,7 +372,7 @@ struct LineFFT {
             exchange(0, 1);
             exchange(1, 2);
         } else {
-            exchange(0, CPT);
+            exchange(0, NV * CPT);
         }
 #pragma unroll
         for (int t = 0; t < R / Rp; ++t) {
@@ -374,13 +382,13 @@ struct LineFFT {
             for (int r = 1; r < Rp; ++r) {
                 const cpx<T> w = PP ? tw[tw_off(PASS) + (r - 1) * Ns + k] : tw[r * k * (N / (Ns * Rp))];
 #pragma unroll
-                for (int cc = 0; cc < CPT; ++cc)
+                for (int cc = 0; cc < NV * CPT; ++cc)
                     v[cc][t * Rp + r] = INV ? cmulc(v[cc][t * Rp + r], w) : cmul(v[cc][t * Rp + r], w);
             }
 #pragma unroll
-            for (int cc = 0; cc < CPT; ++cc) dft<T, Rp, INV>(&v[cc][t * Rp]);
+            for (int cc = 0; cc < NV * CPT; ++cc) dft<T, Rp, INV>(&v[cc][t * Rp]);
         }
-        if constexpr (PASS + 1 < NPASS) pass<INV, PP, PASS + 1, NB, FIRST>(v, buf, c, tw);
+        if constexpr (PASS + 1 < NPASS) pass<INV, PP, PASS + 1, NB, FIRST, NV>(v, buf, c, tw);
     }
 
     // Transform the components this thread carries.  Entry: v[cc][r] = position
@@ -388,12 +396,12 @@ struct LineFFT {
     // tw: the plain table tw[m] = exp(-2 pi i m / N) (PP = false) or its
     // per-pass layout (PP = true); the inverse uses conjugates and is unnormalised.
     // With NB = 2 a following transform starts at buffer (FIRST + NPASS - 1) mod 2.
-    template <bool INV, bool PP = false, int NB = 1, int FIRST = 0>
-    __device__ static __forceinline__ void fft(cpx<T> (&v)[CPT][R], cpx<T>* lds, const Coord& c,
+    template <bool INV, bool PP = false, int NB = 1, int FIRST = 0, int NV = 1>
+    __device__ static __forceinline__ void fft(cpx<T> (*v)[R], cpx<T>* lds, const Coord& c,
                                                const cpx<T>* __restrict__ tw) {
 #pragma unroll
-        for (int cc = 0; cc < CPT; ++cc) dft<T, R, INV>(v[cc]);
-        if constexpr (NPASS > 1) pass<INV, PP, 1, NB, FIRST>(v, lds, c, tw);
+        for (int cc = 0; cc < NV * CPT; ++cc) dft<T, R, INV>(v[cc]);
+        if constexpr (NPASS > 1) pass<INV, PP, 1, NB, FIRST, NV>(v, lds, c, tw);
     }
 };
 

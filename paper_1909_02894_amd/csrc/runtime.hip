@@ -49,12 +49,14 @@ double envelope_at(const dirac_envelope& e, double t) {
 const BisEntry* bis_entries_f64(int* count);
 const BisEntry* bis_entries_f32(int* count);
 
-const BisEntry* bis_entry(int prec, int n, int dir) {
+const BisEntry* bis_entry(int prec, int n, int dir, int nlines) {
     int cnt = 0;
     const BisEntry* e = prec == DIRAC_FP64 ? bis_entries_f64(&cnt) : bis_entries_f32(&cnt);
+    const BisEntry* best = nullptr;
     for (int i = 0; i < cnt; ++i)
-        if (e[i].n == n && e[i].dir == dir) return &e[i];
-    return nullptr;
+        if (e[i].n == n && e[i].dir == dir && e[i].from_lines <= nlines && (!best || e[i].from_lines > best->from_lines))
+            best = &e[i];
+    return best;
 }
 
 std::vector<KernelEntry>& kernel_registry() {
@@ -296,6 +298,9 @@ bool pick_store_mode(int prec, int n, int dir, int other, int mode) {
     // grid narrower than 256 are few, and written through in pieces of a cache
     // line: 64 x 512 FP64 9.6 / 10.2.
     const size_t bytes = (size_t)n * other * 4 * (prec == DIRAC_FP32 ? 4 : 8);
+    // The corrected second-order step's columns beyond 512 points are one-line
+    // tiles with both components per thread (FP32 1024^2 49.3 / 54.8).
+    if ((mode & 4) && dir == 1 && n > 512) return false;
     return bytes <= size_t(prec == DIRAC_FP32 ? 32 : 16) << 20 && (dir == 0 || n <= 256 || other >= 256);
 }
 
@@ -423,7 +428,7 @@ Launch make_launch(const dirac_solver* s, int dir, int e_pre, int e_post, int64_
     if (s->scheme.scheme == DIRAC_SCHEME_EXP_SPLIT_2BIS && (s->curved || s->pml)) {
         // second-order directional step (b = 1 everywhere makes it the plain step)
         const int nlines = dir == 0 ? s->g.n2 : s->g.n1;
-        const BisEntry* e = bis_entry(s->prec, dir == 0 ? s->g.n1 : s->g.n2, dir);
+        const BisEntry* e = bis_entry(s->prec, dir == 0 ? s->g.n1 : s->g.n2, dir, nlines);
         L.fn = e->fn[s->curved ? 1 : 0];
         L.grid = dim3((nlines + e->lines - 1) / e->lines);
         L.block = dim3(e->nthreads);

@@ -37,7 +37,7 @@ template <typename T>
 __device__ void put(void* base, size_t i, double v) { static_cast<T*>(base)[i] = (T)v; }
 
 // Row 0 of the grid writes the axis tables, rows 1..3 the per-pass twiddle
-// layouts (side by side: one after the other in a thread, creation took 57 us longer).
+// layouts.
 __global__ void setup_axis_kernel(SetupAxisParams p) {
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= p.n) return;
