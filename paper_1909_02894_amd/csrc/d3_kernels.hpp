@@ -10,8 +10,6 @@
 //   [Step 1 (and Step 5 of the previous step): psi <- E psi]
 //   psi <- b F^-1[K_i F psi] + (1 - b) psi,  K_i = cos I - i sin alpha^i
 //   [Step 5 after the last step]
-// The two component pairs (u0, u1) and (w0, w1) are transformed one after the
-// other through the same LDS exchange buffer.
 // E = [[e0 I, D g.sigma], [D g.sigma, conj(e0) I]] with e0 = C - i D w, stored per
 // point as (C, -D w, D g_x, D g_y, D g_z) (curved), or diag(e0u, e0u, conj, conj) (flat).
 #pragma once
@@ -26,7 +24,7 @@ struct D3Params {
     const T* E;             // exponential record per point (D3_EREC T), or null (flat)
     const T* inv_s;         // 1/S along the line direction (ones without a layer)
     const cpx<T>* K;        // (cos, sin)(c dt xi) / n
-    const cpx<T>* tw;       // exp(-2 pi i k / n)
+    const cpx<T>* tw;       // exp(-2 pi i m / n) in the per-pass layout of radix d3_radix(n)
     int n1, n2;
     int nlines;
     int e_pre, e_post;
@@ -37,12 +35,14 @@ template <typename T>
 __host__ __device__ constexpr int d3_erec() { return sizeof(T) == 8 ? 6 : 8; }
 template <typename T>
 __host__ __device__ constexpr int d3_radix(int n) { return (sizeof(T) == 8 || n <= 64) ? 4 : 8; }
+// Lines per workgroup: 256 threads (the lines' two half-waves each), one line from
+// 128 threads per pair on.
 template <typename T>
 __host__ __device__ constexpr int d3_lines(int n) {
-    return (n / d3_radix<T>(n)) >= 256 ? 1 : 256 / (n / d3_radix<T>(n));
+    return (n / d3_radix<T>(n)) >= 128 ? 1 : 128 / (n / d3_radix<T>(n));
 }
 template <typename T>
-__host__ __device__ constexpr int d3_threads(int n) { return (n / d3_radix<T>(n)) * d3_lines<T>(n); }
+__host__ __device__ constexpr int d3_threads(int n) { return 2 * (n / d3_radix<T>(n)) * d3_lines<T>(n); }
 
 struct D3Entry {
     int prec, n, dir, lines, nthreads;
@@ -50,33 +50,6 @@ struct D3Entry {
 };
 const D3Entry* d3_entry(int prec, int n, int dir);
 
-template <typename T>
-__device__ __forceinline__ void load_point4(const T* p, uint32_t idx, cpx<T>& u0, cpx<T>& u1, cpx<T>& w0,
-                                            cpx<T>& w1) {
-    const char* b = reinterpret_cast<const char*>(p) + idx * (uint32_t)(8 * sizeof(T));
-    if constexpr (sizeof(T) == 8) {
-        const double2* q = reinterpret_cast<const double2*>(b);
-        const double2 A = q[0], B = q[1], C = q[2], D = q[3];
-        u0 = {A.x, A.y}; u1 = {B.x, B.y}; w0 = {C.x, C.y}; w1 = {D.x, D.y};
-    } else {
-        const float4* q = reinterpret_cast<const float4*>(b);
-        const float4 A = q[0], B = q[1];
-        u0 = {A.x, A.y}; u1 = {A.z, A.w}; w0 = {B.x, B.y}; w1 = {B.z, B.w};
-    }
-}
-template <typename T>
-__device__ __forceinline__ void store_point4(T* p, uint32_t idx, cpx<T> u0, cpx<T> u1, cpx<T> w0, cpx<T> w1) {
-    char* b = reinterpret_cast<char*>(p) + idx * (uint32_t)(8 * sizeof(T));
-    if constexpr (sizeof(T) == 8) {
-        d2v* q = reinterpret_cast<d2v*>(b);
-        gst(q, d2v{u0.re, u0.im}); gst(q + 1, d2v{u1.re, u1.im});
-        gst(q + 2, d2v{w0.re, w0.im}); gst(q + 3, d2v{w1.re, w1.im});
-    } else {
-        f4v* q = reinterpret_cast<f4v*>(b);
-        gst(q, f4v{u0.re, u0.im, u1.re, u1.im});
-        gst(q + 1, f4v{w0.re, w0.im, w1.re, w1.im});
-    }
-}
 // (C, -D w, D g_x, D g_y, D g_z)
 template <typename T>
 __device__ __forceinline__ void load_erec(const T* E, uint32_t idx, T (&e)[5]) {
@@ -93,118 +66,135 @@ __device__ __forceinline__ void load_erec(const T* E, uint32_t idx, T (&e)[5]) {
 }
 
 // DIR 0: x (rows), 1: y, 2: z.  MODE 0 flat, 1 flat + layer, 2 curved.
+//
+// The two component pairs sit in the two halves of a wave: lanes 0..31 carry (u0,
+// u1) and lanes 32..63 (w0, w1) of the same 32 logical threads, and E and K take the
+// other pair from the partner lane.  Against all four components in one thread
+// (pairs transformed one after the other through one buffer): half the registers
+// (226 -> 152 VGPRs for curved FP64 128-point columns, 2 -> 3 waves per SIMD), half the
+// barriers, and every load of the tile issued before the first wait.  Bound by
+// memory: us per step, before / now: 128^3 FP64 curved 268 / 181 (956 MB, 5.3 TB/s),
+// FP32 127 / 98, 64^3 FP64 58 / 41, 256 x 256 x 128 FP32 flat 299 / 257.
 template <typename T, int N, int DIR, int MODE>
 __global__ void __launch_bounds__(d3_threads<T>(N)) d3_stage_kernel(D3Params<T> p) {
     constexpr int R = d3_radix<T>(N), L = d3_lines<T>(N);
-    constexpr bool COLS = DIR != 0;
-    constexpr bool BLEND = MODE != 0;
+    constexpr bool COLS = DIR != 0, BLEND = MODE != 0, PRELOAD_E = MODE == 2 && DIR == 0;
     using F = LineFFT<T, N, R, L, COLS, 2, false>;
     using TS = TwStage<T, N>;
+    static_assert(F::NT % 32 == 0 && !F::SEQ, "whole half-waves, both components exchanged at once");
     constexpr int P = F::P;
-    __shared__ cpx<T> lds[F::LDS_ELEMS];
+    __shared__ cpx<T> lds[2 * F::LDS_ELEMS];
     __shared__ cpx<T> twl[TS::ELEMS];
-    const typename F::Coord c = F::coord(threadIdx.x);
+    const int pair = (threadIdx.x >> 5) & 1, th = ((threadIdx.x >> 6) << 5) | (threadIdx.x & 31);
+    const typename F::Coord c = F::coord(th);
+    cpx<T>* buf = lds + pair * F::LDS_ELEMS;
     const int line = xcd_tile(blockIdx.x, gridDim.x) * L + c.l;
     const bool valid = line < p.nlines;
+    const uint32_t ln = (uint32_t)(valid ? line : p.nlines - 1);     // loads: clamped, branch-free
     const uint32_t n1 = (uint32_t)p.n1, plane = (uint32_t)p.n1 * (uint32_t)p.n2;
-    uint32_t base, stride;
-    if constexpr (DIR == 0) { base = (uint32_t)line * n1; stride = 1; }
-    else if constexpr (DIR == 1) { base = ((uint32_t)line / n1) * plane + (uint32_t)line % n1; stride = n1; }
-    else { base = (uint32_t)line; stride = plane; }
-    auto gidx = [&](int pos) -> uint32_t { return base + (uint32_t)pos * stride; };
+    // point r of this thread: a lane part plus a wave-uniform part r step
+    uint32_t q0, stride;
+    if constexpr (DIR == 0) { q0 = ln * n1; stride = 1; }
+    else if constexpr (DIR == 1) { q0 = (ln / n1) * plane + ln % n1; stride = n1; }
+    else { q0 = ln; stride = plane; }
+    q0 += (uint32_t)c.j * stride;
+    const uint32_t step = P * stride;
+    const uint32_t h0 = 2 * q0 + pair;                               // this thread's half of the point (4 T)
 
-    cpx<T> u[2][R], w[2][R];
+    cpx<T> v[2][R];
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        u[0][r] = u[1][r] = w[0][r] = w[1][r] = cpx<T>{0, 0};
-        if (valid) load_point4(p.psi, gidx(c.j + r * P), u[0][r], u[1][r], w[0][r], w[1][r]);
-    }
+    for (int r = 0; r < R; ++r) load_point(upt(p.psi, 8 * (r * step)), h0, v[0][r], v[1][r]);
+    T e[MODE == 2 ? R : 1][5];
+    auto loadE = [&]() {
+        if constexpr (MODE == 2) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) load_erec(upt(p.E, d3_erec<T>() * (r * step)), q0, e[r]);
+        }
+    };
+    if constexpr (PRELOAD_E) loadE();
     const cpx<T>* tw = p.tw;
-    if constexpr (TS::ON) {                    // unrolled: no wait between the loads
-        cpx<T> twv[F::TW_ITER];
-        F::tw_load(twv, p.tw, threadIdx.x);
-        F::tw_store(twv, twl, threadIdx.x);
-        tw = twl;
-    }
-    auto applyE = [&](int times) {
+    cpx<T> twv[TS::ON ? F::TW_ITER : 1];
+    if constexpr (TS::ON) F::template tw_load<false>(twv, p.tw, th);
+    T b[BLEND ? R : 1];
+    if constexpr (BLEND) {
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            if constexpr (MODE == 2) {
-                T e[5] = {T(1), T(0), T(0), T(0), T(0)};
-                if (valid) load_erec(p.E, gidx(c.j + r * P), e);
-                const cpx<T> e0{e[0], e[1]}, e0c{e[0], -e[1]};
-                const cpx<T> pxy{e[2], -e[3]}, mxy{e[2], e[3]};     // D (g_x - i g_y), D (g_x + i g_y)
-                for (int t = 0; t < times; ++t) {
-                    const cpx<T> a0 = u[0][r], a1 = u[1][r], b0 = w[0][r], b1 = w[1][r];
-                    // D g.sigma v = (D g_z v0 + D(g_x - i g_y) v1, D(g_x + i g_y) v0 - D g_z v1)
-                    u[0][r] = cmul(e0, a0) + scal(e[4], b0) + cmul(pxy, b1);
-                    u[1][r] = cmul(e0, a1) + cmul(mxy, b0) - scal(e[4], b1);
-                    w[0][r] = cmul(e0c, b0) + scal(e[4], a0) + cmul(pxy, a1);
-                    w[1][r] = cmul(e0c, b1) + cmul(mxy, a0) - scal(e[4], a1);
-                }
-            } else {
-                const cpx<T> e0 = p.e0u, e0c{p.e0u.re, -p.e0u.im};
-                for (int t = 0; t < times; ++t) {
-                    u[0][r] = cmul(e0, u[0][r]);
-                    u[1][r] = cmul(e0, u[1][r]);
-                    w[0][r] = cmul(e0c, w[0][r]);
-                    w[1][r] = cmul(e0c, w[1][r]);
+            b[r] = ld_at(p.inv_s + r * P, (uint32_t)c.j);            // ones without a layer
+            if constexpr (MODE == 2) b[r] = ld_at(upt(p.a, r * step), q0) * b[r];
+        }
+    }
+    cpx<T> kk[R];
+#pragma unroll
+    for (int s = 0; s < R; ++s) kk[s] = ld_at(p.K + s * P, (uint32_t)c.j);
+    if constexpr (TS::ON) {
+        if (pair == 0) F::tw_store(twv, twl, th);
+        tw = twl;
+    }
+    // E of the record (C, -D w, D g): the diagonal e0 for u, conj e0 for w; D g.sigma
+    // couples to the other pair
+    auto applyE = [&](int times) {
+        for (int t = 0; t < times; ++t) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                if constexpr (MODE == 2) {
+                    const cpx<T> e0{e[r][0], pair ? -e[r][1] : e[r][1]};
+                    const cpx<T> pxy{e[r][2], -e[r][3]}, mxy{e[r][2], e[r][3]};
+                    const cpx<T> a0 = v[0][r], a1 = v[1][r], b0 = partner(a0), b1 = partner(a1);
+                    v[0][r] = cmul(e0, a0) + scal(e[r][4], b0) + cmul(pxy, b1);
+                    v[1][r] = cmul(e0, a1) + cmul(mxy, b0) - scal(e[r][4], b1);
+                } else {
+                    const cpx<T> e0{p.e0u.re, pair ? -p.e0u.im : p.e0u.im};
+                    v[0][r] = cmul(e0, v[0][r]);
+                    v[1][r] = cmul(e0, v[1][r]);
                 }
             }
         }
     };
-    if (p.e_pre > 0) applyE(p.e_pre);
-    cpx<T> ou[BLEND ? 2 : 1][BLEND ? R : 1], ow[BLEND ? 2 : 1][BLEND ? R : 1];
+    if constexpr (PRELOAD_E) {
+        applyE(p.e_pre);                                             // 1 or 2
+    } else if constexpr (DIR == 0) {                                 // only x launches open with Step 1
+        if (p.e_pre > 0) applyE(p.e_pre);
+    }
+    cpx<T> old[BLEND ? 2 : 1][BLEND ? R : 1];
     if constexpr (BLEND) {
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            ou[0][r] = u[0][r]; ou[1][r] = u[1][r];
-            ow[0][r] = w[0][r]; ow[1][r] = w[1][r];
+            old[0][r] = v[0][r];
+            old[1][r] = v[1][r];
         }
     }
-    F::template fft<false, TS::ON>(u, lds, c, tw);
-    F::template fft<false, TS::ON>(w, lds, c, tw);
+    F::template fft<false, true>(v, buf, c, tw);
 #pragma unroll
     for (int s = 0; s < R; ++s) {
-        const cpx<T> k = p.K[c.j + s * P];
-        const T cs = k.re, sn = k.im;
-        const cpx<T> a0 = u[0][s], a1 = u[1][s], b0 = w[0][s], b1 = w[1][s];
-        if constexpr (DIR == 0) {          // alpha_x: (u, w) -> (sigma_x w, sigma_x u)
-            u[0][s] = scal(cs, a0) + mul_mi(scal(sn, b1));
-            u[1][s] = scal(cs, a1) + mul_mi(scal(sn, b0));
-            w[0][s] = scal(cs, b0) + mul_mi(scal(sn, a1));
-            w[1][s] = scal(cs, b1) + mul_mi(scal(sn, a0));
-        } else if constexpr (DIR == 1) {   // alpha_y: -i sin sigma_y v = sin (-v1, v0)
-            u[0][s] = scal(cs, a0) - scal(sn, b1);
-            u[1][s] = scal(cs, a1) + scal(sn, b0);
-            w[0][s] = scal(cs, b0) - scal(sn, a1);
-            w[1][s] = scal(cs, b1) + scal(sn, a0);
-        } else {                           // alpha_z: -i sin sigma_z v = (-i sin v0, i sin v1)
-            u[0][s] = scal(cs, a0) + mul_mi(scal(sn, b0));
-            u[1][s] = scal(cs, a1) + mul_i(scal(sn, b1));
-            w[0][s] = scal(cs, b0) + mul_mi(scal(sn, a0));
-            w[1][s] = scal(cs, b1) + mul_i(scal(sn, a1));
+        const T cs = kk[s].re, sn = kk[s].im;
+        const cpx<T> a0 = v[0][s], a1 = v[1][s], b0 = partner(a0), b1 = partner(a1);
+        if constexpr (DIR == 0) {                                    // -i sin sigma_x
+            v[0][s] = scal(cs, a0) + mul_mi(scal(sn, b1));
+            v[1][s] = scal(cs, a1) + mul_mi(scal(sn, b0));
+        } else if constexpr (DIR == 1) {                             // -i sin sigma_y = sin (-v1, v0)
+            v[0][s] = scal(cs, a0) - scal(sn, b1);
+            v[1][s] = scal(cs, a1) + scal(sn, b0);
+        } else {                                                     // -i sin sigma_z
+            v[0][s] = scal(cs, a0) + mul_mi(scal(sn, b0));
+            v[1][s] = scal(cs, a1) + mul_i(scal(sn, b1));
         }
     }
-    F::template fft<true, TS::ON>(u, lds, c, tw);
-    F::template fft<true, TS::ON>(w, lds, c, tw);
+    F::template fft<true, true>(v, buf, c, tw);
     if constexpr (BLEND) {
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            const int pos = c.j + r * P;
-            T b = gld(p.inv_s + pos);              // ones without a layer
-            if constexpr (MODE == 2) b = (valid ? ld_at(p.a, gidx(pos)) : T(0)) * b;
-            const T ob = T(1) - b;
-            u[0][r] = scal(b, u[0][r]) + scal(ob, ou[0][r]);
-            u[1][r] = scal(b, u[1][r]) + scal(ob, ou[1][r]);
-            w[0][r] = scal(b, w[0][r]) + scal(ob, ow[0][r]);
-            w[1][r] = scal(b, w[1][r]) + scal(ob, ow[1][r]);
+            const T ob = T(1) - b[r];
+            v[0][r] = scal(b[r], v[0][r]) + scal(ob, old[0][r]);
+            v[1][r] = scal(b[r], v[1][r]) + scal(ob, old[1][r]);
         }
     }
-    if (p.e_post) applyE(1);
+    if (p.e_post) {
+        loadE();
+        applyE(1);
+    }
     if (!valid) return;
 #pragma unroll
-    for (int r = 0; r < R; ++r) store_point4(p.psi, gidx(c.j + r * P), u[0][r], u[1][r], w[0][r], w[1][r]);
+    for (int r = 0; r < R; ++r) store_point(p.psi, h0, v[0][r], v[1][r], 2 * (r * step));
 }
 
 }  // namespace dirac

@@ -33,7 +33,7 @@ namespace {
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 struct Layout3 {
-    size_t psi, a, E, w, scratch, inv_s[3], K[3], D[3], tw[3], partials, out, total;
+    size_t psi, a, E, w, scratch, inv_s[3], K[3], D[3], tw[3], twp[3], partials, out, total;   // twp: per-pass twiddles
 };
 
 struct Setup3Params {
@@ -182,7 +182,8 @@ __global__ void __launch_bounds__(256) d3_obs_kernel(const T* psi, const double*
     double acc[6] = {0, 0, 0, 0, 0, 0};
     for (size_t q = (size_t)blockIdx.x * blockDim.x + threadIdx.x; q < N; q += (size_t)gridDim.x * blockDim.x) {
         cpx<T> u0, u1, w0, w1;
-        load_point4(psi, (uint32_t)q, u0, u1, w0, w1);
+        load_point(psi, 2 * (uint32_t)q, u0, u1);
+        load_point(psi, 2 * (uint32_t)q + 1, w0, w1);
         const double d = (double)u0.re * u0.re + (double)u0.im * u0.im + (double)u1.re * u1.re +
                          (double)u1.im * u1.im + (double)w0.re * w0.re + (double)w0.im * w0.im +
                          (double)w1.re * w1.re + (double)w1.im * w1.im;
@@ -294,6 +295,7 @@ Layout3 layout3(const dirac3_grid* g, const dirac3_metric* m, int32_t prec) {
         L.K[d] = take(ns[d] * 2 * sz);
         L.D[d] = take(ns[d] * sz);
         L.tw[d] = take(ns[d] * 2 * sz);
+        L.twp[d] = take(ns[d] * 2 * sz);
     }
     const size_t setup_parts = ((N + 255) / 256) * 3;
     L.partials = take(std::max(setup_parts, (size_t)kObsBlocks * 8) * 8);
@@ -311,7 +313,7 @@ D3Params<T> d3_params(const dirac3_solver* s, int dir, int e_pre, int e_post) {
     p.E = s->curved ? reinterpret_cast<const T*>(b + s->lay.E) : nullptr;
     p.inv_s = reinterpret_cast<const T*>(b + s->lay.inv_s[dir]);     // ones without a layer
     p.K = reinterpret_cast<const cpx<T>*>(b + s->lay.K[dir]);
-    p.tw = reinterpret_cast<const cpx<T>*>(b + s->lay.tw[dir]);
+    p.tw = reinterpret_cast<const cpx<T>*>(b + s->lay.twp[dir]);
     p.n1 = s->g.n1;
     p.n2 = s->g.n2;
     p.nlines = dir == 0 ? s->g.n2 * s->g.n3 : dir == 1 ? s->g.n1 * s->g.n3 : s->g.n1 * s->g.n2;
@@ -483,6 +485,8 @@ dirac_status dirac3_create(const dirac3_grid* g, const dirac3_metric* m, const d
         ap.K = b + lay.K[d];
         ap.D = b + lay.D[d];
         ap.tw = b + lay.tw[d];
+        const int radix = fp32 ? d3_radix<float>(ns[d]) : d3_radix<double>(ns[d]);
+        ap.twp[twp_index(radix)] = b + lay.twp[d];
         hipError_t e = launch_setup_axis(ap, s->stream);
         if (e != hipSuccess) return bail(fail(DIRAC_E_DEVICE, "setup axis tables: %s", hipGetErrorString(e)));
     }

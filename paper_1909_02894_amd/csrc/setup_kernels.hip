@@ -336,7 +336,7 @@ hipError_t launch_transpose(const void* in, void* out, int n1, int n2, int elem,
 }
 
 hipError_t launch_setup_axis(const SetupAxisParams& p, hipStream_t s) {
-    hipLaunchKernelGGL(setup_axis_kernel, dim3((p.n + 255) / 256, p.twp[0] ? 4 : 1), dim3(256), 0, s, p);
+    hipLaunchKernelGGL(setup_axis_kernel, dim3((p.n + 255) / 256, p.twp[0] || p.twp[1] || p.twp[2] ? 4 : 1), dim3(256), 0, s, p);
     return hipGetLastError();
 }
 hipError_t launch_setup_points(const SetupPointParams& p, double* fold_out, hipStream_t s) {
