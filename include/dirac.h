@@ -297,7 +297,7 @@ dirac_status dirac_set_schedule(dirac_solver* s, int32_t direction, const dirac_
  * which send each line to memory at once instead of leaving it dirty in the
  * XCD's L2 until the kernel ends (0 = ordinary stores).  Write-through pays on
  * small grids whose kernels are latency-bound and loses on large streaming ones:
- * the default goes by the state's size (up to 16 MB in FP64, 32 MB in FP32);
+ * the default goes by the state's size (up to 32 MB, FP64 columns 16 MB);
  * dirac_autotune measures both per direction and keeps the faster.  Results are bitwise the same either way.  Every form
  * of Scheme II's directional step (not Scheme I); write-through for the y
  * kernel only with n2 <= 1024 (else DIRAC_E_ARG). */

@@ -81,12 +81,17 @@ __global__ void __launch_bounds__(bis_threads(N, L, CPT)) bis_stage_kernel(BisPa
             }
         }
     };
+    // point r of this thread: a lane part (line, c.j) plus a wave-uniform part r step
+    const uint32_t ln = gidx(lline, c.j), step = COLS ? P * n1 : P;
+    const PointAt<T, sizeof(T) == 8 && CPT == 2> pt(ln);
+    static_assert(L <= 16, "every line of a tile exists (grids of at least 16 lines): whole waves store");
     // every global load of the tile goes out before the first wait
     cpx<T> v[CPT][R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        if constexpr (CPT == 1) v[0][r] = load_comp(p.psi, gidx(lline, c.j + r * P), c.comp);
-        else load_point(p.psi, gidx(lline, c.j + r * P), v[0][r], v[1][r]);
+        const T* q = upt(p.psi, 4 * (r * step));
+        if constexpr (CPT == 1) v[0][r] = load_comp(q, ln, c.comp);
+        else pt.load(q, v[0][r], v[1][r]);
     }
     // Step 1 / Step 5: row comp of E = [[e0, e1], [conj e1, conj e0]];
     // direction-x launches always open with Step 1 and load E up front
@@ -95,7 +100,7 @@ __global__ void __launch_bounds__(bis_threads(N, L, CPT)) bis_stage_kernel(BisPa
     auto loadE = [&]() {
         if constexpr (MODE == 2) {
 #pragma unroll
-            for (int r = 0; r < R; ++r) load_point(p.E, gidx(lline, c.j + r * P), e0[r], e1[r]);
+            for (int r = 0; r < R; ++r) pt.load(upt(p.E, 4 * (r * step)), e0[r], e1[r]);
         }
     };
     if constexpr (PRELOAD_E) loadE();
@@ -110,9 +115,8 @@ __global__ void __launch_bounds__(bis_threads(N, L, CPT)) bis_stage_kernel(BisPa
         const T s = gld(p.inv_s + pos);            // ones without a layer
         T a = T(1), da = T(0);
         if constexpr (MODE == 2) {
-            const uint32_t q = gidx(lline, pos);
-            a = ld_at(p.a, (uint32_t)lline * N + pos);   // a along this direction's lines
-            da = ld_at(bp.da, 2 * q + dir);
+            a = ld_at(p.a + r * P, (uint32_t)lline * N + c.j);   // a along this direction's lines
+            da = ld_at(upt(bp.da, 2 * (r * step)), 2 * ln + dir);
         }
         b[r] = a * s;
         k2[r] = bp.hh * (b[r] * (T(1) - b[r]));
@@ -221,13 +225,12 @@ __global__ void __launch_bounds__(bis_threads(N, L, CPT)) bis_stage_kernel(BisPa
     const bool wt = (!COLS || N <= kStoreWtMaxColN) && p.wt;       // write-through (as in stage_tile)
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        const uint32_t q = gidx(line, c.j + r * P);
         if constexpr (CPT == 1) {
-            if (wt) store_comp<T, true>(p.psi, q, c.comp, v[0][r]);
-            else store_comp(p.psi, q, c.comp, v[0][r]);
+            if (wt) store_comp<T, true>(p.psi, ln, c.comp, v[0][r], r * step);
+            else store_comp(p.psi, ln, c.comp, v[0][r], r * step);
         } else {
-            if (wt) store_point<T, true>(p.psi, q, v[0][r], v[1][r]);
-            else store_point(p.psi, q, v[0][r], v[1][r]);
+            if (wt) pt.template store<true>(p.psi, v[0][r], v[1][r], r * step);
+            else pt.template store<false>(p.psi, v[0][r], v[1][r], r * step);
         }
     }
 }

@@ -73,20 +73,26 @@ __device__ __forceinline__ void cn_apply_tile(const CnApplyParams& p, int tile, 
     auto gidx = [&](int ln, int pos) -> uint32_t {
         return COLS ? (uint32_t)pos * n1 + ln : (uint32_t)ln * n1 + pos;
     };
+    // point r of this thread: a lane part (line, c.j) plus a wave-uniform part r step
+    const uint32_t ln = gidx(lline, c.j), step = COLS ? P * n1 : P;
+    static_assert(L <= 16, "every line of a tile exists (grids of at least 16 lines): whole waves store");
+    const PointAt<T, CPT == 2> pt(ln);
     // every global load goes out before the first wait
     cpx<T> v[CPT][R], bq[COLS ? 1 : CPT][COLS ? 1 : R];
     T d[R], bf[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        if constexpr (CPT == 1) v[0][r] = load_comp(p.in, gidx(lline, c.j + r * P), c.comp);
-        else load_point(p.in, gidx(lline, c.j + r * P), v[0][r], v[1][r]);
+        const T* q = upt(p.in, 4 * (r * step));
+        if constexpr (CPT == 1) v[0][r] = load_comp(q, ln, c.comp);
+        else pt.load(q, v[0][r], v[1][r]);
     }
     if constexpr (!COLS) {
         if (p.base == 2) {
 #pragma unroll
             for (int r = 0; r < R; ++r) {
-                if constexpr (CPT == 1) bq[0][r] = load_comp(p.b, gidx(lline, c.j + r * P), c.comp);
-                else load_point(p.b, gidx(lline, c.j + r * P), bq[0][r], bq[1][r]);
+                const T* q = upt(p.b, 4 * (r * step));
+                if constexpr (CPT == 1) bq[0][r] = load_comp(q, ln, c.comp);
+                else pt.load(q, bq[0][r], bq[1][r]);
             }
         }
     }
@@ -126,8 +132,8 @@ __device__ __forceinline__ void cn_apply_tile(const CnApplyParams& p, int tile, 
         if (p.vout && valid) {
 #pragma unroll
             for (int r = 0; r < R; ++r) {
-                if constexpr (CPT == 1) store_comp(p.vout, gidx(line, c.j + r * P), c.comp, v[0][r]);
-                else store_point(p.vout, gidx(line, c.j + r * P), v[0][r], v[1][r]);
+                if constexpr (CPT == 1) store_comp(p.vout, ln, c.comp, v[0][r], r * step);
+                else pt.template store<false>(p.vout, v[0][r], v[1][r], r * step);
             }
         }
     }
@@ -153,7 +159,6 @@ __device__ __forceinline__ void cn_apply_tile(const CnApplyParams& p, int tile, 
     if (!valid) return;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        const uint32_t q = gidx(line, c.j + r * P);
         const T f = p.scale * bf[r];               // f c b
         cpx<T> o[CPT];
 #pragma unroll
@@ -164,8 +169,8 @@ __device__ __forceinline__ void cn_apply_tile(const CnApplyParams& p, int tile, 
                 else if (p.base == 2) o[cc] = (bq[cc][r] - in[cc][r]) + o[cc];
             }
         }
-        if constexpr (CPT == 1) store_comp(p.out, q, c.comp, o[0]);
-        else store_point(p.out, q, o[0], o[1]);
+        if constexpr (CPT == 1) store_comp(p.out, ln, c.comp, o[0], r * step);
+        else pt.template store<false>(p.out, o[0], o[1], r * step);
     }
 }
 
@@ -203,15 +208,16 @@ __global__ void cn_exp_kernel(const double* in, double* psi, const double* E, do
     const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= npts) return;
     cpx<double> u, v, e0{e0u.x, e0u.y}, e1{0, 0};
-    load_point(in, (uint32_t)i, u, v);
-    if (E) load_point(E, (uint32_t)i, e0, e1);
+    const PointAt<double, true> pt((uint32_t)i);           // npts is a multiple of the wave
+    pt.load(in, u, v);
+    if (E) pt.load(E, e0, e1);
     for (int t = 0; t < times; ++t) {
         const cpx<double> nu = cmul(e0, u) + cmul(e1, v);
         const cpx<double> nv = cmul(cpx<double>{e0.re, -e0.im}, v) + cmul(cpx<double>{e1.re, -e1.im}, u);
         u = nu;
         v = nv;
     }
-    store_point(psi, (uint32_t)i, u, v);
+    pt.template store<false>(psi, u, v, 0);
 }
 
 // ------------------------------------------------------------ reductions

@@ -20,7 +20,7 @@ const EmEntry* em_entries_f64(int* count) {
 hipError_t launch_em_exp(const double* in, double* out, const double* rec, size_t npts, int times, const double* fA,
                          const double* fV, hipStream_t s) {
     if (times < 1 || times > 2) return hipErrorInvalidValue;
-    EmExpParams<double> p{in, out, rec, npts, times, {fA[0], fA[1]}, {fV[0], fV[1]}};
+    EmExpParams<double> p{in, out, rec, npts, times, {fA[0], fA[1]}, {fV[0], fV[1]}, 0};
     hipLaunchKernelGGL(em_exp_kernel<double>, dim3((unsigned)((npts + 255) / 256)), dim3(256), 0, s, p);
     return hipGetLastError();
 }

@@ -229,7 +229,8 @@ __global__ void __launch_bounds__(em_threads(N, COLS)) em_stage_kernel(EmParams<
 // out <- E(t_1) E(t_0) in (times = 2) or E(t_0) in (times = 1), one thread per
 // point (out may be in): Steps 1 / 5 with potentials, as a pass of their own
 // (Scheme I, and Scheme II on states small enough to stay in the caches, where
-// the direction kernels then run in their plain form).
+// the direction kernels then run in their plain form).  Written through like the x
+// kernels' stores, in whole lines (PointAt): 512^2 FP64 26.5 -> 24.2 us per step.
 template <typename T>
 struct EmExpParams {
     const T* in;
@@ -238,6 +239,7 @@ struct EmExpParams {
     size_t npts;
     int times;
     double fA[2], fV[2];
+    int wt;                      // 1: write-through stores
 };
 
 template <typename T>
@@ -246,10 +248,12 @@ __global__ void __launch_bounds__(256) em_exp_kernel(EmExpParams<T> p) {
     if (i >= p.npts) return;
     cpx<T> u, v;
     double q[6], a;
-    load_point(p.in, (uint32_t)i, u, v);
+    const PointAt<T, sizeof(T) == 8> pt((uint32_t)i);      // npts is a multiple of the wave
+    pt.load(p.in, u, v);
     load_record(p.rec, (uint32_t)i, q, a);
     for (int k = 0; k < p.times; ++k) apply_mat(em_exponential(q, p.fA[k], p.fV[k]), u, v);
-    store_point(p.out, (uint32_t)i, u, v);
+    if (p.wt) pt.template store<true>(p.out, u, v, 0);
+    else pt.template store<false>(p.out, u, v, 0);
 }
 
 }  // namespace dirac

@@ -16,7 +16,7 @@ struct KernelEntry {
     int nthreads;   // workgroup size
     const void* stage_fn[3];   // by mode: 0 flat, 1 flat + layer, 2 curved
     const void* obs_fn;
-    int from_lines[2];         // [flat, blended]: default schedule from this many lines (negative: never)
+    int from_lines[3];         // by mode: default schedule from this many lines (negative: never)
 };
 
 std::vector<KernelEntry>& kernel_registry();
@@ -31,21 +31,22 @@ struct Registrar {
 // float), DIRAC_PREC (0/1), DIRAC_COLS (false/true), DIRAC_DIR (0/1).
 #define DIRAC_CAT2(a, b) a##b
 #define DIRAC_CAT(a, b) DIRAC_CAT2(a, b)
-#define DIRAC_REG_IMPL(N, R, L, CPT, OBS, FLAT, BLEND)                                                \
+#define DIRAC_REG_IMPL(N, R, L, CPT, OBS, FLAT, LAYER, CURVED)                                        \
     static ::dirac::Registrar DIRAC_CAT(reg_, __LINE__)(::dirac::KernelEntry{                        \
         DIRAC_PREC, N, DIRAC_DIR, R, L, CPT,                                                          \
         ::dirac::LineFFT<DIRAC_T, N, R, L, DIRAC_COLS, CPT>::NT,                                       \
         {reinterpret_cast<const void*>(&::dirac::stage_kernel<DIRAC_T, N, R, L, DIRAC_COLS, 0, CPT>), \
          reinterpret_cast<const void*>(&::dirac::stage_kernel<DIRAC_T, N, R, L, DIRAC_COLS, 1, CPT>), \
          reinterpret_cast<const void*>(&::dirac::stage_kernel<DIRAC_T, N, R, L, DIRAC_COLS, 2, CPT>)},\
-        OBS, {FLAT, BLEND}});
-// REG: a direction-kernel schedule.  REGD: one that is the default of flat grids
-// (FLAT) and of grids with a layer or a metric (BLEND) that have at least that
-// many lines, up to the next threshold (a negative number: never).  REGO / REGOD:
+        OBS, {FLAT, LAYER, CURVED}});
+// REG: a direction-kernel schedule.  REGD: one that is the default of grids with at
+// least so many lines, up to the next threshold (a negative number: never), per
+// mode: flat, flat with a layer, curved.  REGO / REGOD:
 // the same plus the observable kernel with that schedule (one per precision, n
 // and direction).
-#define REG(N, R, L, CPT) DIRAC_REG_IMPL(N, R, L, CPT, nullptr, -1, -1)
-#define REGD(N, R, L, CPT, FLAT, BLEND) DIRAC_REG_IMPL(N, R, L, CPT, nullptr, FLAT, BLEND)
+#define REG(N, R, L, CPT) DIRAC_REG_IMPL(N, R, L, CPT, nullptr, -1, -1, -1)
+#define REGD(N, R, L, CPT, FLAT, LAYER, CURVED) DIRAC_REG_IMPL(N, R, L, CPT, nullptr, FLAT, LAYER, CURVED)
 #define DIRAC_OBS(N, R, L, CPT) reinterpret_cast<const void*>(&::dirac::obs_kernel<DIRAC_T, N, R, L, DIRAC_COLS, CPT>)
-#define REGO(N, R, L, CPT) DIRAC_REG_IMPL(N, R, L, CPT, DIRAC_OBS(N, R, L, CPT), -1, -1)
-#define REGOD(N, R, L, CPT, FLAT, BLEND) DIRAC_REG_IMPL(N, R, L, CPT, DIRAC_OBS(N, R, L, CPT), FLAT, BLEND)
+#define REGO(N, R, L, CPT) DIRAC_REG_IMPL(N, R, L, CPT, DIRAC_OBS(N, R, L, CPT), -1, -1, -1)
+#define REGOD(N, R, L, CPT, FLAT, LAYER, CURVED) \
+    DIRAC_REG_IMPL(N, R, L, CPT, DIRAC_OBS(N, R, L, CPT), FLAT, LAYER, CURVED)

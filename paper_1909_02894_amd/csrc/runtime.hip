@@ -242,13 +242,13 @@ const KernelEntry* find_entry(int prec, int n, int dir, const dirac_schedule& s)
     return nullptr;
 }
 // Default schedule of `lines` lines of n points: the entry with the largest
-// threshold not above it, for flat or blended (layer or metric) kernels.
-const KernelEntry* default_entry(int prec, int n, int dir, int lines, bool blended) {
+// threshold not above it, for the kernels of a mode (0 flat, 1 layer, 2 curved).
+const KernelEntry* default_entry(int prec, int n, int dir, int lines, int mode) {
     const KernelEntry* best = nullptr;
     for (const auto& e : kernel_registry()) {
-        const int from = e.from_lines[blended ? 1 : 0];
+        const int from = e.from_lines[mode];
         if (e.prec == prec && e.n == n && e.dir == dir && from >= 0 && from <= lines &&
-            (!best || from > best->from_lines[blended ? 1 : 0]))
+            (!best || from > best->from_lines[mode]))
             best = &e;
     }
     return best;
@@ -290,18 +290,19 @@ bool pick_store_mode(int prec, int n, int dir, int other, int mode) {
         if (it != tune_cache().end()) return it->second.wt != 0;
     }
     // Not tuned: write-through on the grids whose kernels otherwise end waiting
-    // for the write-back of their stores, i.e. states up to 16 MB (32 MB in
-    // FP32).  us per step, ordinary / written through, default schedules: curved
-    // FP64 512^2 24.8 / 17.4, 1024 x 256 25.7 / 17.0, FP32 1024^2 34.5 / 27.3,
-    // 4096 x 512 54.1 / 49.7; larger ones gain little or lose: curved FP64 1024^2 54.1 / 64.1,
-    // 2048 x 512 48.9 / 51.8.  Columns longer than 256 points of a
-    // grid narrower than 256 are few, and written through in pieces of a cache
-    // line: 64 x 512 FP64 9.6 / 10.2.
+    // for the write-back of their stores, i.e. states up to 32 MB (FP64 columns: 16
+    // MB).  us per step, ordinary / written through, default schedules: curved FP64
+    // 512^2 24.8 / 17.4, 1024 x 256 25.7 / 17.0, FP32 1024^2 34.5 / 27.3, 4096 x 512 54.1 /
+    // 49.7, FP64 1024^2 rows 49.9 / 48.5, its columns 48.5 / 48.7; larger ones gain
+    // little or lose (FP64 4096^2 rows curved 923 / 923, flat 639 / 728).  Columns
+    // longer than 256 points of a grid narrower than 256 are few, and written through
+    // in pieces of a cache line: 64 x 512 FP64 9.6 / 10.2.
     const size_t bytes = (size_t)n * other * 4 * (prec == DIRAC_FP32 ? 4 : 8);
     // The corrected second-order step's columns beyond 512 points are one-line
     // tiles with both components per thread (FP32 1024^2 49.3 / 54.8).
     if ((mode & 4) && dir == 1 && n > 512) return false;
-    return bytes <= size_t(prec == DIRAC_FP32 ? 32 : 16) << 20 && (dir == 0 || n <= 256 || other >= 256);
+    if (dir == 0) return bytes <= size_t(32) << 20;
+    return bytes <= size_t(prec == DIRAC_FP32 ? 32 : 16) << 20 && (n <= 256 || other >= 256);
 }
 
 const KernelEntry* pick_entry(int prec, int n, int dir, int other, int mode) {
@@ -313,7 +314,7 @@ const KernelEntry* pick_entry(int prec, int n, int dir, int other, int mode) {
             if (const KernelEntry* e = find_entry(prec, n, dir, sc)) return e;
         }
     }
-    return default_entry(prec, n, dir, other, (mode & 3) != 0);
+    return default_entry(prec, n, dir, other, (mode & 2) ? 2 : mode & 1);
 }
 
 // ---------------------------------------------------------------- launches
@@ -473,7 +474,7 @@ Launch make_exp_launch(const dirac_solver* s, int times, int64_t step) {
     L.block = dim3(256);
     auto fill = [&](auto* psi, auto* rec) {
         using T = std::remove_const_t<std::remove_pointer_t<decltype(rec)>>;
-        EmExpParams<T> p{psi, psi, rec, npts, times, {0, 0}, {0, 0}};
+        EmExpParams<T> p{psi, psi, rec, npts, times, {0, 0}, {0, 0}, s->store_wt[0] ? 1 : 0};
         for (int k = 0; k < times; ++k) {
             p.fA[k] = envelope_at(s->env_A, t[k]);
             p.fV[k] = envelope_at(s->env_V, t[k]);

@@ -95,6 +95,75 @@ __device__ __forceinline__ void load_point(const T* p, uint32_t idx, cpx<T>& u, 
         v = {(T)A.z, (T)A.w};
     }
 }
+// FP64 points in accesses that cover whole cache lines.  A thread that holds both
+// components reads its 32-byte point as two 16-byte pieces, and each of the wave's
+// two accesses touches half of every line.  Instead the half-waves share: access A
+// reads the points of lanes 0..31 (component 0 in those lanes, component 1 in their
+// partners lane xor 32), access B those of lanes 32..63, and one half-wave swap
+// per word puts each point into its own lane (stores: the swap first).  us per
+// launch, plain / shared: FP64 2048 rows radix 8 flat 79 / 70, curved 100 / 95,
+// columns 99 / 90 and 113 / 104; 4096 curved rows 610 / 423, columns 585 / 495;
+// 1024 curved columns radix 8 x 2 lines 34 / 26.
+struct PairOffsets { uint32_t a, b; };         // byte offsets of a lane's part of accesses A and B
+__device__ __forceinline__ PairOffsets pair_offsets(uint32_t idx) {
+    const uint32_t other = partner_u32(idx);
+    return (threadIdx.x & 32) ? PairOffsets{other * 32 + 16, idx * 32 + 16} : PairOffsets{idx * 32, other * 32};
+}
+// upper half of A <-> lower half of B
+__device__ __forceinline__ void swap_halves(d2v& A, d2v& B) {
+    u32x4 a = __builtin_bit_cast(u32x4, A), b = __builtin_bit_cast(u32x4, B);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const auto r = __builtin_amdgcn_permlane32_swap(a[k], b[k], false, false);
+        a[k] = r[0];
+        b[k] = r[1];
+    }
+    A = __builtin_bit_cast(d2v, a);
+    B = __builtin_bit_cast(d2v, b);
+}
+__device__ __forceinline__ void load_points(const double* p, PairOffsets o, cpx<double>& u, cpx<double>& v) {
+    const char* c = reinterpret_cast<const char*>(p);
+    d2v A = gld(reinterpret_cast<const d2v*>(c + o.a)), B = gld(reinterpret_cast<const d2v*>(c + o.b));
+    swap_halves(A, B);
+    u = {A.x, A.y};
+    v = {B.x, B.y};
+}
+template <bool WT = false>
+__device__ __forceinline__ void store_points(double* p, PairOffsets o, cpx<double> u, cpx<double> v, uint32_t uidx = 0) {
+    d2v A{u.re, u.im}, B{v.re, v.im};
+    swap_halves(A, B);
+    if constexpr (WT) {
+        gst_wt16(p, o.a, __builtin_bit_cast(u32x4, A), uidx * 32);
+        gst_wt16(p, o.b, __builtin_bit_cast(u32x4, B), uidx * 32);
+    } else {
+        char* c = reinterpret_cast<char*>(upt(p, 4 * uidx));
+        gst(reinterpret_cast<d2v*>(c + o.a), A);
+        gst(reinterpret_cast<d2v*>(c + o.b), B);
+    }
+}
+// A point (idx + a wave-uniform part in the base or uidx) by either way: plain
+// accesses, or (PAIRED, FP64) those above, which need every lane of the wave.
+template <typename T, bool PAIRED>
+struct PointAt {
+    uint32_t idx;
+    __device__ __forceinline__ explicit PointAt(uint32_t i) : idx(i) {}
+    __device__ __forceinline__ void load(const T* p, cpx<T>& u, cpx<T>& v) const { load_point(p, idx, u, v); }
+    template <bool WT>
+    __device__ __forceinline__ void store(T* p, cpx<T> u, cpx<T> v, uint32_t uidx) const {
+        store_point<T, WT>(p, idx, u, v, uidx);
+    }
+};
+template <>
+struct PointAt<double, true> {
+    PairOffsets o;
+    __device__ __forceinline__ explicit PointAt(uint32_t i) : o(pair_offsets(i)) {}
+    __device__ __forceinline__ void load(const double* p, cpx<double>& u, cpx<double>& v) const { load_points(p, o, u, v); }
+    template <bool WT>
+    __device__ __forceinline__ void store(double* p, cpx<double> u, cpx<double> v, uint32_t uidx) const {
+        store_points<WT>(p, o, u, v, uidx);
+    }
+};
+
 // Longest column line whose kernel carries the write-through store path.
 constexpr int kStoreWtMaxColN = 1024;
 
@@ -196,6 +265,12 @@ __device__ __forceinline__ void stage_tile(const StageParams<T>& p, int tile, cp
     // the a table is laid out along this direction's lines (transposed for columns)
     const uint32_t aln = (uint32_t)lline * N + c.j;
     const uint32_t sstep = COLS ? P * pitch : P, estep = COLS ? P * n1 : P;
+    // FP64 points by shared accesses; not in the flat radix-16 tiles of up to 256
+    // threads, which hold two waves per SIMD with no register to spare (2048 columns
+    // 77 / 93 us, 4096 rows 280 / 533).  Grids are powers of two from 16 points, so a
+    // tile of up to 16 lines is never cut and all its lanes reach the stores.
+    constexpr bool PAIRED = sizeof(T) == 8 && CPT == 2 && L <= 16 && !(R == 16 && MODE != 2 && F::NT <= 256);
+    const PointAt<T, PAIRED> spt(sln), ept(eln);
     // v[cc][r] <- f(own, other, component, r) for every carried component
     auto mix = [&](cpx<T> (&a)[CPT][R], auto&& f) {
 #pragma unroll
@@ -219,7 +294,7 @@ __device__ __forceinline__ void stage_tile(const StageParams<T>& p, int tile, cp
     for (int r = 0; r < R; ++r) {
         const T* q = upt(p.psi, 4 * (r * sstep));
         if constexpr (CPT == 1) v[0][r] = load_comp(q, sln, c.comp);
-        else load_point(q, sln, v[0][r], v[1][r]);
+        else spt.load(q, v[0][r], v[1][r]);
     }
     // Step 1 (and Step 5 of the previous step): row `comp` of
     // E = [[e0, e1], [conj e1, conj e0]]: A own + B other with A = e0, B = e1 for
@@ -231,7 +306,7 @@ __device__ __forceinline__ void stage_tile(const StageParams<T>& p, int tile, cp
     auto loadE = [&]() {
         if constexpr (MODE == 2) {
 #pragma unroll
-            for (int r = 0; r < R; ++r) load_point(upt(p.E, 4 * (r * estep)), eln, e0[r], e1[r]);
+            for (int r = 0; r < R; ++r) ept.load(upt(p.E, 4 * (r * estep)), e0[r], e1[r]);
         }
     };
     auto applyE = [&](int times) {
@@ -321,7 +396,7 @@ __device__ __forceinline__ void stage_tile(const StageParams<T>& p, int tile, cp
             for (int r = 0; r < R; ++r) {
                 const T* q = upt(p.psi, 4 * (r * sstep));
                 if constexpr (CPT == 1) old[0][r] = load_comp(q, sln, c.comp);
-                else load_point(q, sln, old[0][r], old[1][r]);
+                else spt.load(q, old[0][r], old[1][r]);
             }
         }
         if constexpr (!PF) blend_weights();
@@ -344,13 +419,13 @@ __device__ __forceinline__ void stage_tile(const StageParams<T>& p, int tile, cp
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             if constexpr (CPT == 1) store_comp<T, true>(p.psi, sln, c.comp, v[0][r], r * sstep);
-            else store_point<T, true>(p.psi, sln, v[0][r], v[1][r], r * sstep);
+            else spt.template store<true>(p.psi, v[0][r], v[1][r], r * sstep);
         }
     } else {
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             if constexpr (CPT == 1) store_comp(p.psi, sln, c.comp, v[0][r], r * sstep);
-            else store_point(p.psi, sln, v[0][r], v[1][r], r * sstep);
+            else spt.template store<false>(p.psi, v[0][r], v[1][r], r * sstep);
         }
     }
 }
