@@ -98,7 +98,7 @@ __device__ __forceinline__ void cn_apply_tile(const CnApplyParams& p, int tile, 
     }
     const cpx<T>* tw = p.tw;
     cpx<T> twv[TS::ON ? F::TW_ITER : 1];
-    if constexpr (TS::ON) F::tw_load(twv, p.tw, threadIdx.x);
+    if constexpr (TS::ON) F::template tw_load<false>(twv, p.tw, threadIdx.x);
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         d[r] = gld(p.D + c.j + r * P);
@@ -132,17 +132,22 @@ __device__ __forceinline__ void cn_apply_tile(const CnApplyParams& p, int tile, 
         if (p.vout && valid) {
 #pragma unroll
             for (int r = 0; r < R; ++r) {
-                if constexpr (CPT == 1) store_comp(p.vout, ln, c.comp, v[0][r], r * step);
-                else pt.template store<false>(p.vout, v[0][r], v[1][r], r * step);
+                if constexpr (CPT == 1) {
+                    if (p.wt) store_comp<T, true>(p.vout, ln, c.comp, v[0][r], r * step);
+                    else store_comp(p.vout, ln, c.comp, v[0][r], r * step);
+                } else {
+                    if (p.wt) pt.template store<true>(p.vout, v[0][r], v[1][r], r * step);
+                    else pt.template store<false>(p.vout, v[0][r], v[1][r], r * step);
+                }
             }
         }
     }
-    F::template fft<false, TS::ON>(v, lds, c, tw);
+    F::template fft<false, true>(v, lds, c, tw);
 #pragma unroll
     for (int cc = 0; cc < CPT; ++cc)
 #pragma unroll
         for (int s = 0; s < R; ++s) v[cc][s] = mul_i(scal(d[s], v[cc][s]));
-    F::template fft<true, TS::ON>(v, lds, c, tw);
+    F::template fft<true, true>(v, lds, c, tw);
     // sigma_i [[d_i]] v: rows (sigma_x) t0 = [[d]] v1, t1 = [[d]] v0; columns
     // (sigma_y) t0 = -i [[d]] v1, t1 = i [[d]] v0
     cpx<T> tq[CPT][R];
@@ -169,8 +174,13 @@ __device__ __forceinline__ void cn_apply_tile(const CnApplyParams& p, int tile, 
                 else if (p.base == 2) o[cc] = (bq[cc][r] - in[cc][r]) + o[cc];
             }
         }
-        if constexpr (CPT == 1) store_comp(p.out, ln, c.comp, o[0], r * step);
-        else pt.template store<false>(p.out, o[0], o[1], r * step);
+        if constexpr (CPT == 1) {
+            if (p.wt) store_comp<T, true>(p.out, ln, c.comp, o[0], r * step);
+            else store_comp(p.out, ln, c.comp, o[0], r * step);
+        } else {
+            if (p.wt) pt.template store<true>(p.out, o[0], o[1], r * step);
+            else pt.template store<false>(p.out, o[0], o[1], r * step);
+        }
     }
 }
 
@@ -204,7 +214,8 @@ __global__ void __launch_bounds__((CnTile<N, true, true>::NT)) cn_apply2_kernel(
 
 // psi <- E^times in (times = 1 or 2; psi may be in), E = [[e0, e1], [conj e1, conj e0]]
 // per point, or the uniform diagonal diag(e0u, conj e0u) when E is null.
-__global__ void cn_exp_kernel(const double* in, double* psi, const double* E, double2 e0u, size_t npts, int times) {
+__global__ void cn_exp_kernel(const double* in, double* psi, const double* E, double2 e0u, size_t npts, int times,
+                              int wt) {
     const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= npts) return;
     cpx<double> u, v, e0{e0u.x, e0u.y}, e1{0, 0};
@@ -217,7 +228,15 @@ __global__ void cn_exp_kernel(const double* in, double* psi, const double* E, do
         u = nu;
         v = nv;
     }
-    pt.template store<false>(psi, u, v, 0);
+    if (wt) pt.template store<true>(psi, u, v, 0);
+    else pt.template store<false>(psi, u, v, 0);
+}
+
+// Entry i of a vector (wave-uniform base).
+__device__ __forceinline__ void put2(double* base, size_t i, double2 v, int wt) {
+    const d2v x{v.x, v.y};
+    if (wt) gst_wt16(base, (uint32_t)i * 16, __builtin_bit_cast(u32x4, x));
+    else gst(reinterpret_cast<d2v*>(base) + i, x);
 }
 
 // ------------------------------------------------------------ reductions
@@ -417,17 +436,16 @@ __global__ void cn_init_kernel(CnCtrl* c, double hdt, double rtol, int max_iter,
 // rhs <- rx + ry, x <- 2 rhs - x (the first-order predictor of the solution,
 // psi - dt A psi), ||rhs||; the step's counters are reset.
 __global__ void __launch_bounds__(kCnThreads) cn_rhs_kernel(const double* rx, const double* ry, double* rhs,
-                                                             double* x, size_t ncplx, double* partials) {
+                                                             double* x, size_t ncplx, double* partials, int wt) {
     double ar[1] = {0.0}, ai[1] = {0.0};
     const double2* RX = reinterpret_cast<const double2*>(rx);
     const double2* RY = reinterpret_cast<const double2*>(ry);
-    double2* B = reinterpret_cast<double2*>(rhs);
-    double2* X = reinterpret_cast<double2*>(x);
+    const double2* X = reinterpret_cast<const double2*>(x);
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < ncplx; i += (size_t)gridDim.x * blockDim.x) {
         const double2 a = RX[i], b = RY[i], h = X[i];
         const double2 r = {a.x + b.x, a.y + b.y};
-        B[i] = r;
-        X[i] = make_double2(2.0 * r.x - h.x, 2.0 * r.y - h.y);
+        put2(rhs, i, r, wt);
+        put2(x, i, make_double2(2.0 * r.x - h.x, 2.0 * r.y - h.y), wt);
         ar[0] += r.x * r.x + r.y * r.y;
     }
     store_partials<1>(ar, ai, partials, 1);       // slot 1: read with the first residual's (slot 0)
@@ -435,14 +453,14 @@ __global__ void __launch_bounds__(kCnThreads) cn_rhs_kernel(const double* rx, co
 
 // r <- rx + ry (in ry) and ||r||^2; see launch_cn_residual.
 __global__ void __launch_bounds__(kCnThreads) cn_residual_kernel(const double* rx, double* ry, size_t ncplx,
-                                                                  double* partials) {
+                                                                  double* partials, int wt) {
     double ar[1] = {0.0}, ai[1] = {0.0};
     const double2* RX = reinterpret_cast<const double2*>(rx);
-    double2* RY = reinterpret_cast<double2*>(ry);
+    const double2* RY = reinterpret_cast<const double2*>(ry);
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < ncplx; i += (size_t)gridDim.x * blockDim.x) {
         const double2 a = RX[i], b = RY[i];
         const double2 r = {a.x + b.x, a.y + b.y};
-        RY[i] = r;
+        put2(ry, i, r, wt);
         ar[0] += r.x * r.x + r.y * r.y;
     }
     store_partials<1>(ar, ai, partials, 0);
@@ -455,11 +473,11 @@ __global__ void __launch_bounds__(kCnThreads) cn_residual_kernel(const double* r
 template <int NK, bool FIRST>
 __global__ void __launch_bounds__(kCnThreads) cn_gs1_kernel(const double* V, size_t vstride, int k0, int j,
                                                              double* wx, const double* wy, size_t ncplx,
-                                                             double* partials) {
+                                                             double* partials, int wt) {
     double ar[NK], ai[NK], nr[1] = {0.0}, ni[1] = {0.0};
 #pragma unroll
     for (int k = 0; k < NK; ++k) ar[k] = ai[k] = 0.0;
-    double2* W = reinterpret_cast<double2*>(wx);
+    const double2* W = reinterpret_cast<const double2*>(wx);
     const double2* WY = reinterpret_cast<const double2*>(wy);
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < ncplx; i += (size_t)gridDim.x * blockDim.x) {
         double2 x = W[i];
@@ -471,7 +489,7 @@ __global__ void __launch_bounds__(kCnThreads) cn_gs1_kernel(const double* V, siz
                 const double2 b = WY[i];
                 x.x += b.x;
                 x.y += b.y;
-                W[i] = x;
+                put2(wx, i, x, wt);
             }
         }
 #pragma unroll
@@ -583,11 +601,11 @@ __global__ void __launch_bounds__(kCnThreads) cn_finish_kernel(const double* par
 template <int NKR>
 __global__ void __launch_bounds__(kCnThreads) cn_gs_update_kernel(double* V, size_t vstride, int nfull, int j,
                                                                    const double* w, size_t ncplx, const double* rec,
-                                                                   const CnCtrl* c) {
+                                                                   const CnCtrl* c, int wt) {
     const double* coef = rec;
     const double hn = c->hn;
     const double alpha = hn > 0.0 ? 1.0 / hn : 0.0;
-    double2* out = reinterpret_cast<double2*>(V + (size_t)(j + 1) * vstride);
+    double* out = V + (size_t)(j + 1) * vstride;
     const double2* Wi = reinterpret_cast<const double2*>(w);
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < ncplx; i += (size_t)gridDim.x * blockDim.x) {
         double2 x = Wi[i];
@@ -613,7 +631,7 @@ __global__ void __launch_bounds__(kCnThreads) cn_gs_update_kernel(double* V, siz
         }
         x.x *= alpha;
         x.y *= alpha;
-        out[i] = x;
+        put2(out, i, x, wt);
     }
 }
 
@@ -627,7 +645,7 @@ template <int NKR>
 __global__ void __launch_bounds__(kCnThreads) cn_update_kernel(const double* V, size_t vstride, int nfull,
                                                                 double* x, double* r_out, size_t ncplx,
                                                                 const double* rec, double* partials,
-                                                                const CnCtrl* c) {
+                                                                const CnCtrl* c, int wt) {
     constexpr int M1 = kCnMaxRestart + 1;
     // the least-squares state of up to nq = nv - 1 columns, packed: R column l
     // (rows 0..l) at l (l + 1) / 2, H_A column j (rows 0..j + 1) at j (j + 3) / 2;
@@ -691,8 +709,7 @@ __global__ void __launch_bounds__(kCnThreads) cn_update_kernel(const double* V, 
     }
     __syncthreads();
     double rr[1] = {0.0}, ri[1] = {0.0};
-    double2* X = reinterpret_cast<double2*>(x);
-    double2* RO = reinterpret_cast<double2*>(r_out);
+    const double2* X = reinterpret_cast<const double2*>(x);
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < ncplx; i += (size_t)gridDim.x * blockDim.x) {
         double2 v = X[i], r = {0.0, 0.0};
         for (int c8 = 0; c8 < nfull; ++c8) {
@@ -719,8 +736,8 @@ __global__ void __launch_bounds__(kCnThreads) cn_update_kernel(const double* V, 
             r.x += cr[2 * l] * b[q].x - cr[2 * l + 1] * b[q].y;
             r.y += cr[2 * l] * b[q].y + cr[2 * l + 1] * b[q].x;
         }
-        X[i] = v;
-        RO[i] = r;
+        put2(x, i, v, wt);
+        put2(r_out, i, r, wt);
         rr[0] += r.x * r.x + r.y * r.y;
     }
     store_partials<1>(rr, ri, partials, 0);
@@ -750,6 +767,8 @@ static hipError_t launch_apply_dir(int n, int nlines, const CnApplyParams& p, hi
     return hipGetLastError();
 }
 
+int cn_twiddle_radix(int n, int dir, bool merged) { return merged ? cn2_radix(n) : cn_radix(n, dir == 1); }
+
 hipError_t launch_cn_apply(int dir, int n, int nlines, const CnApplyParams& p, hipStream_t s) {
     return dir == 0 ? launch_apply_dir<false>(n, nlines, p, s) : launch_apply_dir<true>(n, nlines, p, s);
 }
@@ -771,9 +790,9 @@ hipError_t launch_cn_apply2(int n, const CnApplyParams& px, const CnApplyParams&
 }
 
 hipError_t launch_cn_exp(const double* in, double* out, const double* E, double e0r, double e0i, size_t npts,
-                         int times, hipStream_t s) {
+                         int times, bool wt, hipStream_t s) {
     hipLaunchKernelGGL(cn_exp_kernel, dim3((unsigned)((npts + 255) / 256)), dim3(256), 0, s, in, out, E,
-                       make_double2(e0r, e0i), npts, times);
+                       make_double2(e0r, e0i), npts, times, (int)wt);
     return hipGetLastError();
 }
 
@@ -790,14 +809,16 @@ static hipError_t finish(const double* partials, int nslots, CnFinish kind, int 
 }
 
 hipError_t launch_cn_rhs(const double* rx, const double* ry, double* rhs, double* x, size_t ncplx, double* partials,
-                         hipStream_t s) {
-    hipLaunchKernelGGL(cn_rhs_kernel, dim3(kCnDotBlocks), dim3(kCnThreads), 0, s, rx, ry, rhs, x, ncplx, partials);
+                         bool wt, hipStream_t s) {
+    hipLaunchKernelGGL(cn_rhs_kernel, dim3(kCnDotBlocks), dim3(kCnThreads), 0, s, rx, ry, rhs, x, ncplx, partials,
+                       (int)wt);
     return hipGetLastError();
 }
 
-hipError_t launch_cn_residual(const double* rx, double* ry, size_t ncplx, double* partials, CnCtrl* ctrl,
+hipError_t launch_cn_residual(const double* rx, double* ry, size_t ncplx, double* partials, CnCtrl* ctrl, bool wt,
                               hipStream_t s) {
-    hipLaunchKernelGGL(cn_residual_kernel, dim3(kCnDotBlocks), dim3(kCnThreads), 0, s, rx, ry, ncplx, partials);
+    hipLaunchKernelGGL(cn_residual_kernel, dim3(kCnDotBlocks), dim3(kCnThreads), 0, s, rx, ry, ncplx, partials,
+                       (int)wt);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     return finish(partials, 2, kFinStart, 0, nullptr, ctrl, s);
@@ -807,7 +828,7 @@ hipError_t launch_cn_residual(const double* rx, double* ry, size_t ncplx, double
 // vectors, one launch each (the first also forms w = wx + wy and its norm),
 // then the finishing workgroup.
 hipError_t launch_cn_gs1(const double* V, size_t vstride, int j, double* wx, const double* wy, size_t ncplx,
-                         double* partials, double* rec, CnCtrl* ctrl, hipStream_t s) {
+                         double* partials, double* rec, CnCtrl* ctrl, bool wt, hipStream_t s) {
     if (j < 0 || j >= kCnMaxRestart) return hipErrorInvalidValue;
     const int nk = j + 1;
     const int nchunks = (nk + kCnChunk - 1) / kCnChunk;
@@ -817,10 +838,10 @@ hipError_t launch_cn_gs1(const double* V, size_t vstride, int j, double* wx, con
     case NK:                                                                                                     \
         if (ch == 0)                                                                                             \
             hipLaunchKernelGGL((cn_gs1_kernel<NK, true>), dim3(kCnDotBlocks), dim3(kCnThreads), 0, s, V, vstride,\
-                               k0, j, wx, wy, ncplx, partials);                                                  \
+                               k0, j, wx, wy, ncplx, partials, (int)wt);                                         \
         else                                                                                                     \
             hipLaunchKernelGGL((cn_gs1_kernel<NK, false>), dim3(kCnDotBlocks), dim3(kCnThreads), 0, s, V,        \
-                               vstride, k0, j, wx, wy, ncplx, partials);                                         \
+                               vstride, k0, j, wx, wy, ncplx, partials, (int)wt);                                \
         break;
         switch (cnt) {
             DIRAC_CN_GS(1) DIRAC_CN_GS(2) DIRAC_CN_GS(3) DIRAC_CN_GS(4)
@@ -833,13 +854,13 @@ hipError_t launch_cn_gs1(const double* V, size_t vstride, int j, double* wx, con
 }
 
 hipError_t launch_cn_gs_update(double* V, size_t vstride, int j, const double* w, size_t ncplx, const double* rec,
-                               CnCtrl* ctrl, hipStream_t s) {
+                               CnCtrl* ctrl, bool wt, hipStream_t s) {
     if (j < 0 || j >= kCnMaxRestart) return hipErrorInvalidValue;
     const int nk = j + 1, nfull = nk / 8;
 #define DIRAC_CN_UP(R)                                                                                           \
     case R:                                                                                                      \
         hipLaunchKernelGGL((cn_gs_update_kernel<R>), dim3(1024), dim3(kCnThreads), 0, s, V, vstride, nfull, j, w,\
-                           ncplx, rec, (const CnCtrl*)ctrl);                                                     \
+                           ncplx, rec, (const CnCtrl*)ctrl, (int)wt);                                            \
         break;
     switch (nk % 8) {
         DIRAC_CN_UP(0) DIRAC_CN_UP(1) DIRAC_CN_UP(2) DIRAC_CN_UP(3)
@@ -851,13 +872,13 @@ hipError_t launch_cn_gs_update(double* V, size_t vstride, int j, const double* w
 }
 
 hipError_t launch_cn_update(const double* V, size_t vstride, int nk, double* x, double* r_out, size_t ncplx,
-                            const double* rec, double* partials, CnCtrl* ctrl, CnHead* host, hipStream_t s) {
+                            const double* rec, double* partials, CnCtrl* ctrl, CnHead* host, bool wt, hipStream_t s) {
     if (nk < 0 || nk > kCnMaxRestart) return hipErrorInvalidValue;
     const int nv = nk + 1, nfull = nv / 8;
 #define DIRAC_CN_XU(R)                                                                                           \
     case R:                                                                                                      \
         hipLaunchKernelGGL((cn_update_kernel<R>), dim3(kCnDotBlocks), dim3(kCnThreads), 0, s, V, vstride, nfull, \
-                           x, r_out, ncplx, rec, partials, (const CnCtrl*)ctrl);                                 \
+                           x, r_out, ncplx, rec, partials, (const CnCtrl*)ctrl, (int)wt);                        \
         break;
     switch (nv % 8) {
         DIRAC_CN_XU(0) DIRAC_CN_XU(1) DIRAC_CN_XU(2) DIRAC_CN_XU(3)

@@ -67,21 +67,32 @@ struct CnApplyParams {
     const double* a;         // a(x) along this direction's lines (a[line * n + pos]), or null (a = 1)
     const double* inv_s;     // 1/S along the line direction (ones without a layer)
     const double* D;         // xi / n along the line direction
-    const cpx<double>* tw;   // twiddles
+    const cpx<double>* tw;   // twiddles in the per-pass layout of cn_twiddle_radix
     const int* gate;         // skip the launch when gate[0] == 0 (null: always run)
     int n1;                  // points per row
     int nlines;
     int base;                // 0: none, 1: v, 2: b - v (x pass only)
     double scale;            // f c
+    int wt;                  // 1: write-through stores
 };
 
+// Radix of the kernel launch_cn_apply (merged: launch_cn_apply2) runs for n-point lines.
+int cn_twiddle_radix(int n, int dir, bool merged);
 hipError_t launch_cn_apply(int dir, int n, int nlines, const CnApplyParams& p, hipStream_t s);
 // Both directions of a square n x n grid (n <= 512) in one launch (px: x pass,
 // py: y pass); the gate is px's.
 hipError_t launch_cn_apply2(int n, const CnApplyParams& px, const CnApplyParams& py, hipStream_t s);
 // out <- E^times in per point (E = diag(e0, conj e0) when E is null); out may be in.
 hipError_t launch_cn_exp(const double* in, double* out, const double* E, double e0r, double e0i, size_t npts,
-                         int times, hipStream_t s);
+                         int times, bool wt, hipStream_t s);
+
+// wt below: write-through stores of the vectors, for states of 4 to 16 MB, whose
+// kernels otherwise end waiting for the write-back of what they stored (us per step,
+// ordinary / written through: 512 x 256 203 / 195, 512^2 214 / 209, 1024 x 512
+// 388 / 369; smaller states have little to wait for: 64 x 1024 196 / 205).
+constexpr bool cn_write_through(size_t state_bytes) {
+    return state_bytes >= (size_t(4) << 20) && state_bytes <= (size_t(16) << 20);
+}
 
 // The reductions below run kCnDotBlocks workgroups of 256 threads over the ncplx
 // complex entries of the vectors; each workgroup writes fixed-order partial
@@ -93,26 +104,26 @@ hipError_t launch_cn_init(CnCtrl* ctrl, double hdt, double rtol, int max_iter, i
 // rhs <- rx + ry; x <- 2 rhs - x; the partial sums of ||rhs||^2 (finished with
 // the first residual's).
 hipError_t launch_cn_rhs(const double* rx, const double* ry, double* rhs, double* x, size_t ncplx, double* partials,
-                         hipStream_t s);
+                         bool wt, hipStream_t s);
 // The step's first residual r <- rx + ry (in ry), then with ||rhs|| (bnorm,
 // tol = rtol bnorm, the step's counters reset): converged if ||r|| <= tol, else
 // a new cycle from r.
-hipError_t launch_cn_residual(const double* rx, double* ry, size_t ncplx, double* partials, CnCtrl* ctrl,
+hipError_t launch_cn_residual(const double* rx, double* ry, size_t ncplx, double* partials, CnCtrl* ctrl, bool wt,
                               hipStream_t s);
 // Arnoldi iteration j (basis V, vstride doubles apart), classical Gram-Schmidt:
 // w <- wx + wy (in wx); h_k = <V_k, w> (k <= j), hn = ||w - V h||; the Givens
 // update of column j.
 hipError_t launch_cn_gs1(const double* V, size_t vstride, int j, double* wx, const double* wy, size_t ncplx,
-                         double* partials, double* rec, CnCtrl* ctrl, hipStream_t s);
+                         double* partials, double* rec, CnCtrl* ctrl, bool wt, hipStream_t s);
 // V_{j+1} = (w - sum h_k V_k) / hn.
 hipError_t launch_cn_gs_update(double* V, size_t vstride, int j, const double* w, size_t ncplx, const double* rec,
-                               CnCtrl* ctrl, hipStream_t s);
+                               CnCtrl* ctrl, bool wt, hipStream_t s);
 // The end of a cycle (gated on ctrl->done): x += V y with R y = g solved per
 // workgroup, and the residual r = rhs - G x = V (beta e_0 - H_G y) from the
 // Arnoldi relation to r_out with its norm; then the outcome (converged, out of
 // iterations, or a restart from r).  nk = columns queued (>= the cycle's k).
 // Then the state head is written to `host` (pinned host memory), every time.
 hipError_t launch_cn_update(const double* V, size_t vstride, int nk, double* x, double* r_out, size_t ncplx,
-                            const double* rec, double* partials, CnCtrl* ctrl, CnHead* host, hipStream_t s);
+                            const double* rec, double* partials, CnCtrl* ctrl, CnHead* host, bool wt, hipStream_t s);
 
 }  // namespace dirac

@@ -53,6 +53,7 @@ struct CnCtx {
     CnHead* head;                     // pinned host copy of the state head (written by a kernel)
     hipEvent_t ev;                    // recorded after the kernel that writes the head
     int j;                            // columns queued in the current cycle
+    bool wt;                          // write-through vector stores
 
     double* vec(int k) const { return V + (size_t)k * vstride; }
     double* rec_of(int j) const { return rec + (size_t)j * kCnRecDoubles; }
@@ -69,6 +70,8 @@ hipError_t apply(const CnCtx& c, const double* in, const double* in_norm, double
                  double f, const int* gate) {
     dirac_solver* s = c.s;
     char* b = s->base;
+    // square grids up to 512 points: both directions in one launch, side by side
+    const bool merged = s->g.n1 == s->g.n2 && s->g.n1 <= 512;
     CnApplyParams pp[2];
     for (int dir = 0; dir < 2; ++dir) {
         CnApplyParams& p = pp[dir];
@@ -82,15 +85,16 @@ hipError_t apply(const CnCtx& c, const double* in, const double* in_norm, double
         p.a = s->curved ? reinterpret_cast<const double*>(b + (dir == 0 ? s->lay.a : s->lay.aT)) : nullptr;
         p.inv_s = reinterpret_cast<const double*>(b + s->lay.inv_s[dir]);   // ones without a layer
         p.D = reinterpret_cast<const double*>(b + s->lay.D[dir]);
-        p.tw = reinterpret_cast<const cpx<double>*>(b + s->lay.tw[dir]);
+        const int radix = cn_twiddle_radix(dir == 0 ? s->g.n1 : s->g.n2, dir, merged);
+        p.tw = reinterpret_cast<const cpx<double>*>(b + s->lay.twp[dir][twp_index(radix)]);
         p.gate = gate;
         p.n1 = s->g.n1;
         p.nlines = dir == 0 ? s->g.n2 : s->g.n1;
         p.base = dir == 0 ? base : 0;
         p.scale = f * s->g.c;
+        p.wt = c.wt ? 1 : 0;
     }
-    // square grids up to 512 points: both directions in one launch, side by side
-    if (s->g.n1 == s->g.n2 && s->g.n1 <= 512) return launch_cn_apply2(s->g.n1, pp[0], pp[1], c.st);
+    if (merged) return launch_cn_apply2(s->g.n1, pp[0], pp[1], c.st);
     for (int dir = 0; dir < 2; ++dir) {
         hipError_t e = launch_cn_apply(dir, dir == 0 ? s->g.n1 : s->g.n2, pp[dir].nlines, pp[dir], c.st);
         if (e != hipSuccess) return e;
@@ -106,16 +110,16 @@ hipError_t arnoldi(const CnCtx& c, int j) {
     if (j == 0) e = apply(c, c.wy, &c.ctrl->beta, c.vec(0), 0, nullptr, 1.0, nullptr);
     else e = apply(c, c.vec(j), nullptr, nullptr, 0, nullptr, 1.0, nullptr);
     if (e != hipSuccess) return e;
-    if ((e = launch_cn_gs1(c.V, c.vstride, j, c.wx, c.wy, c.ncplx, c.part, c.rec_of(j), c.ctrl, c.st)) != hipSuccess)
+    if ((e = launch_cn_gs1(c.V, c.vstride, j, c.wx, c.wy, c.ncplx, c.part, c.rec_of(j), c.ctrl, c.wt, c.st)) != hipSuccess)
         return e;
-    return launch_cn_gs_update(c.V, c.vstride, j, c.wx, c.ncplx, c.rec_of(j), c.ctrl, c.st);
+    return launch_cn_gs_update(c.V, c.vstride, j, c.wx, c.ncplx, c.rec_of(j), c.ctrl, c.wt, c.st);
 }
 
 // The end of the queued iterations: the end-of-cycle kernels (the update is a
 // no-op until the cycle has ended; the finish writes the state head to the
 // pinned host copy every time) and the event the host waits for.
 hipError_t close_batch(CnCtx& c) {
-    hipError_t e = launch_cn_update(c.V, c.vstride, c.j, c.psi, c.wy, c.ncplx, c.rec, c.part, c.ctrl, c.head, c.st);
+    hipError_t e = launch_cn_update(c.V, c.vstride, c.j, c.psi, c.wy, c.ncplx, c.rec, c.part, c.ctrl, c.head, c.wt, c.st);
     if (e == hipSuccess) e = hipEventRecord(c.ev, c.st);
     return e;
 }
@@ -135,9 +139,9 @@ hipError_t begin_solve(CnCtx& c, int batch) {
     dirac_solver* s = c.s;
     const double hdt = 0.5 * s->g.dt;
     hipError_t e = apply(c, c.psi, nullptr, nullptr, 1, nullptr, -hdt, nullptr);
-    if (e == hipSuccess) e = launch_cn_rhs(c.wx, c.wy, c.rhs, c.psi, c.ncplx, c.part, c.st);
+    if (e == hipSuccess) e = launch_cn_rhs(c.wx, c.wy, c.rhs, c.psi, c.ncplx, c.part, c.wt, c.st);
     if (e == hipSuccess) e = apply(c, c.psi, nullptr, nullptr, 2, c.rhs, -hdt, nullptr);
-    if (e == hipSuccess) e = launch_cn_residual(c.wx, c.wy, c.ncplx, c.part, c.ctrl, c.st);
+    if (e == hipSuccess) e = launch_cn_residual(c.wx, c.wy, c.ncplx, c.part, c.ctrl, c.wt, c.st);
     c.j = 0;
     if (e == hipSuccess) e = queue_iterations(c, std::min(batch, s->scheme.gmres_restart));
     return e;
@@ -216,6 +220,7 @@ dirac_status cn_step_n(dirac_solver* s, int64_t nsteps) {
         c.head = static_cast<CnHead*>(s->cn_head) + k;
         c.ev = s->cn_ev[k];
         c.j = 0;
+        c.wt = cn_write_through(c.npts * 32);
     }
     const double* E = s->curved ? reinterpret_cast<const double*>(b + s->lay.E) : nullptr;
     // Step 3 of the previous step, then Step 1 of this one (one application when
@@ -223,7 +228,7 @@ dirac_status cn_step_n(dirac_solver* s, int64_t nsteps) {
     // time-dependent potentials the two use t_{n-1/2} and t_{n+1/2}
     const size_t npts = cx[0].npts;
     auto exp_steps = [&](int64_t n_abs, int times, bool closing, const double* in, double* out) -> hipError_t {
-        if (!s->has_em) return launch_cn_exp(in, out, E, s->e0u_re, s->e0u_im, npts, times, s->stream);
+        if (!s->has_em) return launch_cn_exp(in, out, E, s->e0u_re, s->e0u_im, npts, times, cx[0].wt, s->stream);
         const double dt = s->g.dt;
         double t[2];
         if (closing) t[0] = (n_abs + 0.5) * dt;
