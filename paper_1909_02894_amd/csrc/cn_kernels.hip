@@ -241,13 +241,14 @@ __device__ __forceinline__ void put2(double* base, size_t i, double2 v, int wt) 
 
 // ------------------------------------------------------------ reductions
 
-constexpr int kCnThreads = 256;
-constexpr int kCnSlots = kCnMaxRestart + 2;      // partial slots per workgroup (complex)
-static_assert(kCnDotBlocks % 32 == 0, "the final sums take 32 workgroups per lane");
+constexpr int kCnThreads = 512;
+constexpr int kCnWaves = kCnThreads / 64;
+constexpr int kCnSlots = kCnMaxRestart + 2;      // partial slots (complex): [slot][workgroup]
+static_assert(kCnDotBlocks % 32 == 0, "32 lanes per slot in the final sums");
 
 // Fixed-order workgroup sum of NS complex values per thread: a 64-lane
-// butterfly, then the four waves in order; slot s0 + k of this workgroup's
-// partials receives value k.
+// butterfly, then the waves in order; slot s0 + k of this workgroup's partials
+// receives value k.
 template <int NS>
 __device__ __forceinline__ void store_partials(double (&ar)[NS], double (&ai)[NS], double* partials, int s0) {
 #pragma unroll
@@ -258,7 +259,7 @@ __device__ __forceinline__ void store_partials(double (&ar)[NS], double (&ai)[NS
             ai[k] += __shfl_xor(ai[k], off);
         }
     }
-    __shared__ double sr[NS][4], si[NS][4];
+    __shared__ double sr[NS][kCnWaves], si[NS][kCnWaves];
     const int wave = threadIdx.x >> 6;
     if ((threadIdx.x & 63) == 0) {
 #pragma unroll
@@ -270,9 +271,15 @@ __device__ __forceinline__ void store_partials(double (&ar)[NS], double (&ai)[NS
     __syncthreads();
     if ((int)threadIdx.x < NS) {
         const int k = threadIdx.x;
-        double* o = partials + 2 * ((size_t)blockIdx.x * kCnSlots + s0 + k);
-        o[0] = ((sr[k][0] + sr[k][1]) + sr[k][2]) + sr[k][3];
-        o[1] = ((si[k][0] + si[k][1]) + si[k][2]) + si[k][3];
+        double r = sr[k][0], i = si[k][0];
+#pragma unroll
+        for (int w = 1; w < kCnWaves; ++w) {
+            r += sr[k][w];
+            i += si[k][w];
+        }
+        double* o = partials + 2 * ((size_t)(s0 + k) * kCnDotBlocks + blockIdx.x);
+        o[0] = r;
+        o[1] = i;
     }
 }
 
@@ -290,7 +297,7 @@ __device__ void final_sums(const double* partials, int nslots, double* out) {
             double2 v[PER];
 #pragma unroll
             for (int q = 0; q < PER; ++q)
-                v[q] = *reinterpret_cast<const double2*>(partials + 2 * ((size_t)(lane + 32 * q) * kCnSlots + sl));
+                v[q] = *reinterpret_cast<const double2*>(partials + 2 * ((size_t)sl * kCnDotBlocks + lane + 32 * q));
 #pragma unroll
             for (int q = 0; q < PER; ++q) {
                 r += v[q].x;
@@ -468,8 +475,7 @@ __global__ void __launch_bounds__(kCnThreads) cn_residual_kernel(const double* r
 
 // First Gram-Schmidt pass of Arnoldi iteration j, basis vectors k0 .. k0+NK-1 of
 // this launch: dots with w (FIRST: w = wx + wy is formed and stored to wx, and
-// ||w||^2 goes to slot j + 1).  The last workgroup of the last launch stores the
-// coefficients and decides: a second pass, or the Givens update of column j.
+// ||w||^2 goes to slot j + 1).
 template <int NK, bool FIRST>
 __global__ void __launch_bounds__(kCnThreads) cn_gs1_kernel(const double* V, size_t vstride, int k0, int j,
                                                              double* wx, const double* wy, size_t ncplx,
@@ -508,130 +514,147 @@ __global__ void __launch_bounds__(kCnThreads) cn_gs1_kernel(const double* V, siz
 
 // What the finishing workgroup does with the final sums of a reduction.
 // kFinStart: ||rhs||^2 in slot 1 and the first residual's norm in slot 0;
-// kFinRes: the residual after a cycle; kFinGs: the Gram-Schmidt dots of an iteration.
-enum CnFinish { kFinStart = 1, kFinRes = 2, kFinGs = 3 };
+// kFinRes: the residual after a cycle.
+enum CnFinish { kFinStart = 1, kFinRes = 2 };
 
-// One workgroup after each reduction kernel: the final sums of its partials,
-// then the solve-state update of `kind` (thread 0) and, after the Gram-Schmidt
-// dots of an Arnoldi iteration, the Givens update of column j.  Every load of
+// One workgroup after a residual's reduction kernel: the final sums of its
+// partials, then the solve-state update of `kind` (thread 0).  Every load of
 // the solve state is issued with the partials' loads (one memory round trip).
 // After a cycle (kFinRes), the head of the state is also written to `host`
 // (pinned host memory) for the host's decision.
-__global__ void __launch_bounds__(kCnThreads) cn_finish_kernel(const double* partials, int nslots, int kind, int j,
-                                                                double* rec, CnCtrl* c, CnHead* host) {
-    constexpr int M1 = kCnMaxRestart + 1;
+__global__ void __launch_bounds__(kCnThreads) cn_finish_kernel(const double* partials, int nslots, int kind,
+                                                                CnCtrl* c, CnHead* host) {
     __shared__ double s[2 * kCnSlots];
-    __shared__ double h[2 * M1], cs[M1], sn[2 * M1];
-    __shared__ double hn_s;
-    const int t = threadIdx.x;
-    const bool gs = kind == kFinGs;
-    double pc = 0.0, pr = 0.0, pi = 0.0;
-    if (gs && t < j) {
-        pc = c->cs[t];
-        pr = c->sn[2 * t];
-        pi = c->sn[2 * t + 1];
-    }
-    const CtrlSnap q = load_snap(c, j, gs);
+    const CtrlSnap q = load_snap(c, 0, false);
     final_sums(partials, nslots, s);
     // after a cycle's end: nothing to decide while the cycle goes on, nor when it
     // ended with no column (the first residual met the tolerance; the update
     // kernel wrote nothing)
     const bool decide = kind != kFinRes || !(q.done == 0 || (q.k == 0 && !q.nonfinite));
-    if (gs && t < j) {
-        cs[t] = pc;
-        sn[2 * t] = pr;
-        sn[2 * t + 1] = pi;
-    }
-    if (t == 0 && decide) {
-        if (kind == kFinStart || kind == kFinRes) {
-            const double r2 = s[0];
-            double tol = q.tol;
-            int nonfinite = q.nonfinite;
-            if (kind == kFinStart) {               // the step's right-hand side: counters reset
-                const double b2 = s[2];
-                tol = q.rtol * sqrt(b2);
-                nonfinite = isfinite(b2) ? 0 : 1;
-                c->bnorm = sqrt(b2);
-                c->tol = tol;
-                c->used = 0;
-                c->k = 0;                          // no column yet: the update leaves x as it is
-            }
-            c->res2 = r2;
-            if (!isfinite(r2) || nonfinite) {
-                c->nonfinite = 1;
-                c->done = 1;
-                c->state = 3;
-            } else if (sqrt(r2) <= tol) {
-                c->nonfinite = 0;
-                c->done = 1;
-                c->state = 2;
-            } else if (kind == kFinRes && q.used >= q.max_iter) {
-                c->state = 3;
-            } else {
-                c->nonfinite = 0;
-                start_cycle(c, sqrt(r2));
-                if (kind == kFinRes) c->state = 1;
-            }
+    if (threadIdx.x != 0) return;
+    if (decide) {
+        const double r2 = s[0];
+        double tol = q.tol;
+        int nonfinite = q.nonfinite;
+        if (kind == kFinStart) {                   // the step's right-hand side: counters reset
+            const double b2 = s[2];
+            tol = q.rtol * sqrt(b2);
+            nonfinite = isfinite(b2) ? 0 : 1;
+            c->bnorm = sqrt(b2);
+            c->tol = tol;
+            c->used = 0;
+            c->k = 0;                              // no column yet: the update leaves x as it is
+        }
+        c->res2 = r2;
+        if (!isfinite(r2) || nonfinite) {
+            c->nonfinite = 1;
+            c->done = 1;
+            c->state = 3;
+        } else if (sqrt(r2) <= tol) {
+            c->nonfinite = 0;
+            c->done = 1;
+            c->state = 2;
+        } else if (kind == kFinRes && q.used >= q.max_iter) {
+            c->state = 3;
         } else {
-            double* h1 = rec;                      // Gram-Schmidt coefficients, slots 0..j
-            double p2 = 0.0;
-            for (int k = 0; k <= j; ++k) {
-                h1[2 * k] = h[2 * k] = s[2 * k];
-                h1[2 * k + 1] = h[2 * k + 1] = s[2 * k + 1];
-                p2 += s[2 * k] * s[2 * k] + s[2 * k + 1] * s[2 * k + 1];
-            }
-            const double w2 = s[2 * (j + 1)];
-            const double n2 = w2 - p2;             // ||w - V h||^2 with an orthonormal basis
-            hn_s = isfinite(w2) ? sqrt(n2 > 0.0 ? n2 : 0.0) : NAN;
-            c->hn = hn_s;
-            h1[2 * (j + 1)] = hn_s;                // the subdiagonal entry, for the residual
-            h1[2 * (j + 1) + 1] = 0.0;
+            c->nonfinite = 0;
+            start_cycle(c, sqrt(r2));
+            if (kind == kFinRes) c->state = 1;
         }
     }
-    __syncthreads();
-    if (gs) givens_column(c, j, h, hn_s, q, cs, sn);
-    if (host && t == 0) {                          // this thread wrote c's head above
+    if (host) {                                    // this thread wrote c's head above
         const CnHead* hd = reinterpret_cast<const CnHead*>(c);
         *host = *hd;
     }
 }
 
-// V_{j+1} <- (w - sum_{k<=j} h_k V_k) / ctrl->hn (0 for hn = 0), j + 1 = 8 nfull +
-// NKR coefficients.
+// ||w - V h|| from the dots s[0..j] and ||w||^2 in s[j + 1] (complex slots), with
+// an orthonormal basis; NaN for a non-finite w.
+__device__ __forceinline__ double new_norm(const double* s, int j) {
+    double p2 = 0.0;
+    for (int k = 0; k <= j; ++k) p2 += s[2 * k] * s[2 * k] + s[2 * k + 1] * s[2 * k + 1];
+    const double w2 = s[2 * (j + 1)], n2 = w2 - p2;
+    return isfinite(w2) ? sqrt(n2 > 0.0 ? n2 : 0.0) : NAN;
+}
+
+// The Gram-Schmidt coefficients and the Givens update of column j (one workgroup).
+__device__ void finish_column(const double* partials, int j, double* rec, CnCtrl* c) {
+    constexpr int M1 = kCnMaxRestart + 1;
+    __shared__ double s[2 * kCnSlots], cs[M1], sn[2 * M1];
+    const int t = threadIdx.x;
+    if (t < j) {
+        cs[t] = c->cs[t];
+        sn[2 * t] = c->sn[2 * t];
+        sn[2 * t + 1] = c->sn[2 * t + 1];
+    }
+    const CtrlSnap q = load_snap(c, j, true);
+    final_sums(partials, j + 2, s);
+    const double hn = new_norm(s, j);
+    if (t <= j) {
+        rec[2 * t] = s[2 * t];
+        rec[2 * t + 1] = s[2 * t + 1];
+    }
+    if (t == 0) {
+        rec[2 * (j + 1)] = hn;                     // the subdiagonal entry, for the residual
+        rec[2 * (j + 1) + 1] = 0.0;
+    }
+    givens_column(c, j, s, hn, q, cs, sn);
+}
+
+// V_{j+1} <- (w - sum_{k<=j} h_k V_k) / hn (0 for hn = 0), j + 1 = 8 nfull + NKR
+// coefficients.  Every workgroup takes the final sums of the dots itself (the
+// same order in each, 4 KB per slot from the L2, behind the loads of its first
+// entries), while workgroup 0 does the Givens update of the column: a launch of its
+// own between the two kernels held the chip for 4.7 us and a launch gap per
+// iteration (512^2: 209 -> 199 us per step).  256 workgroups of 512 threads keep
+// what each must sum small (512 of 512: 208 us, 512 of 256: 200, and 2048^2
+// 4212 / 4291 / 4248).
 template <int NKR>
 __global__ void __launch_bounds__(kCnThreads) cn_gs_update_kernel(double* V, size_t vstride, int nfull, int j,
-                                                                   const double* w, size_t ncplx, const double* rec,
-                                                                   const CnCtrl* c, int wt) {
-    const double* coef = rec;
-    const double hn = c->hn;
-    const double alpha = hn > 0.0 ? 1.0 / hn : 0.0;
+                                                                   const double* w, size_t ncplx,
+                                                                   const double* partials, double* rec, CnCtrl* c,
+                                                                   int wt) {
+    if (blockIdx.x == 0) {
+        finish_column(partials, j, rec, c);
+        return;
+    }
+    __shared__ double coef[2 * kCnSlots];
     double* out = V + (size_t)(j + 1) * vstride;
     const double2* Wi = reinterpret_cast<const double2*>(w);
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < ncplx; i += (size_t)gridDim.x * blockDim.x) {
-        double2 x = Wi[i];
-        for (int c8 = 0; c8 < nfull; ++c8) {
-            double2 y[8];
+    const size_t stride = (size_t)(gridDim.x - 1) * blockDim.x;
+    constexpr int NR = NKR > 0 ? NKR : 1;
+    double2 x, y[NR];
+    auto load = [&](size_t i) {
+        x = Wi[i];
 #pragma unroll
-            for (int k = 0; k < 8; ++k) y[k] = reinterpret_cast<const double2*>(V + (size_t)(8 * c8 + k) * vstride)[i];
+        for (int k = 0; k < NKR; ++k) y[k] = reinterpret_cast<const double2*>(V + (size_t)(8 * nfull + k) * vstride)[i];
+    };
+    size_t i = (size_t)(blockIdx.x - 1) * blockDim.x + threadIdx.x;
+    if (i < ncplx) load(i);
+    final_sums(partials, j + 2, coef);
+    const double hn = new_norm(coef, j);
+    const double alpha = hn > 0.0 ? 1.0 / hn : 0.0;
+    while (i < ncplx) {
+        for (int c8 = 0; c8 < nfull; ++c8) {
+            double2 z[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) z[k] = reinterpret_cast<const double2*>(V + (size_t)(8 * c8 + k) * vstride)[i];
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
                 const double cr = coef[2 * (8 * c8 + k)], ci = coef[2 * (8 * c8 + k) + 1];
-                x.x -= cr * y[k].x - ci * y[k].y;
-                x.y -= cr * y[k].y + ci * y[k].x;
+                x.x -= cr * z[k].x - ci * z[k].y;
+                x.y -= cr * z[k].y + ci * z[k].x;
             }
         }
-        double2 y[NKR > 0 ? NKR : 1];
-#pragma unroll
-        for (int k = 0; k < NKR; ++k) y[k] = reinterpret_cast<const double2*>(V + (size_t)(8 * nfull + k) * vstride)[i];
 #pragma unroll
         for (int k = 0; k < NKR; ++k) {
             const double cr = coef[2 * (8 * nfull + k)], ci = coef[2 * (8 * nfull + k) + 1];
             x.x -= cr * y[k].x - ci * y[k].y;
             x.y -= cr * y[k].y + ci * y[k].x;
         }
-        x.x *= alpha;
-        x.y *= alpha;
-        put2(out, i, x, wt);
+        put2(out, i, make_double2(alpha * x.x, alpha * x.y), wt);
+        i += stride;
+        if (i < ncplx) load(i);
     }
 }
 
@@ -801,10 +824,9 @@ hipError_t launch_cn_init(CnCtrl* ctrl, double hdt, double rtol, int max_iter, i
     return hipGetLastError();
 }
 
-static hipError_t finish(const double* partials, int nslots, CnFinish kind, int j, double* rec, CnCtrl* ctrl,
-                         hipStream_t s, CnHead* host = nullptr) {
-    hipLaunchKernelGGL(cn_finish_kernel, dim3(1), dim3(kCnThreads), 0, s, partials, nslots, (int)kind, j, rec, ctrl,
-                       host);
+static hipError_t finish(const double* partials, int nslots, CnFinish kind, CnCtrl* ctrl, hipStream_t s,
+                         CnHead* host = nullptr) {
+    hipLaunchKernelGGL(cn_finish_kernel, dim3(1), dim3(kCnThreads), 0, s, partials, nslots, (int)kind, ctrl, host);
     return hipGetLastError();
 }
 
@@ -821,14 +843,13 @@ hipError_t launch_cn_residual(const double* rx, double* ry, size_t ncplx, double
                        (int)wt);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    return finish(partials, 2, kFinStart, 0, nullptr, ctrl, s);
+    return finish(partials, 2, kFinStart, ctrl, s);
 }
 
 // Gram-Schmidt dots of Arnoldi iteration j: with V_0 .. V_j in chunks of kCnChunk
-// vectors, one launch each (the first also forms w = wx + wy and its norm),
-// then the finishing workgroup.
+// vectors, one launch each (the first also forms w = wx + wy and its norm).
 hipError_t launch_cn_gs1(const double* V, size_t vstride, int j, double* wx, const double* wy, size_t ncplx,
-                         double* partials, double* rec, CnCtrl* ctrl, bool wt, hipStream_t s) {
+                         double* partials, bool wt, hipStream_t s) {
     if (j < 0 || j >= kCnMaxRestart) return hipErrorInvalidValue;
     const int nk = j + 1;
     const int nchunks = (nk + kCnChunk - 1) / kCnChunk;
@@ -850,17 +871,17 @@ hipError_t launch_cn_gs1(const double* V, size_t vstride, int j, double* wx, con
         }
 #undef DIRAC_CN_GS
     }
-    return finish(partials, j + 2, kFinGs, j, rec, ctrl, s);
+    return hipGetLastError();
 }
 
-hipError_t launch_cn_gs_update(double* V, size_t vstride, int j, const double* w, size_t ncplx, const double* rec,
-                               CnCtrl* ctrl, bool wt, hipStream_t s) {
+hipError_t launch_cn_gs_update(double* V, size_t vstride, int j, const double* w, size_t ncplx,
+                               const double* partials, double* rec, CnCtrl* ctrl, bool wt, hipStream_t s) {
     if (j < 0 || j >= kCnMaxRestart) return hipErrorInvalidValue;
     const int nk = j + 1, nfull = nk / 8;
 #define DIRAC_CN_UP(R)                                                                                           \
     case R:                                                                                                      \
-        hipLaunchKernelGGL((cn_gs_update_kernel<R>), dim3(1024), dim3(kCnThreads), 0, s, V, vstride, nfull, j, w,\
-                           ncplx, rec, (const CnCtrl*)ctrl, (int)wt);                                            \
+        hipLaunchKernelGGL((cn_gs_update_kernel<R>), dim3(kCnDotBlocks + 1), dim3(kCnThreads), 0, s, V, vstride,  \
+                           nfull, j, w, ncplx, partials, rec, ctrl, (int)wt);                                    \
         break;
     switch (nk % 8) {
         DIRAC_CN_UP(0) DIRAC_CN_UP(1) DIRAC_CN_UP(2) DIRAC_CN_UP(3)
@@ -888,7 +909,7 @@ hipError_t launch_cn_update(const double* V, size_t vstride, int nk, double* x, 
 #undef DIRAC_CN_XU
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    return finish(partials, 1, kFinRes, 0, nullptr, ctrl, s, host);
+    return finish(partials, 1, kFinRes, ctrl, s, host);
 }
 
 }  // namespace dirac

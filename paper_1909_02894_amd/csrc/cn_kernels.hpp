@@ -8,7 +8,7 @@
 
 namespace dirac {
 
-constexpr int kCnDotBlocks = 512;     // workgroups of the reduction kernels
+constexpr int kCnDotBlocks = 256;     // workgroups of the reduction kernels
 constexpr int kCnMaxRestart = 63;     // Krylov vectors per cycle (validated on creation)
 constexpr int kCnChunk = 8;           // basis vectors one reduction launch handles
 
@@ -22,7 +22,7 @@ struct CnCtrl {
     double bnorm;         // ||rhs||
     double tol;           // rtol ||rhs||
     double res2;          // squared norm of the last explicit residual
-    double hn;            // norm of the newest Arnoldi vector before normalisation
+    double pad3;
     double hdt;           // dt / 2 (G = I + hdt A)
     double rtol;
     double pad0;
@@ -44,7 +44,7 @@ struct CnCtrl {
 
 // The first 96 bytes of CnCtrl, which the host reads after a cycle.
 struct CnHead {
-    double beta, bnorm, tol, res2, hn, hdt, rtol, pad0;
+    double beta, bnorm, tol, res2, pad3, hdt, rtol, pad0;
     int k, done, used, max_iter, m, state, nonfinite, pad1;
 };
 static_assert(sizeof(CnHead) == 96 && offsetof(CnCtrl, pad2) == sizeof(CnHead), "CnCtrl head layout");
@@ -94,10 +94,10 @@ constexpr bool cn_write_through(size_t state_bytes) {
     return state_bytes >= (size_t(4) << 20) && state_bytes <= (size_t(16) << 20);
 }
 
-// The reductions below run kCnDotBlocks workgroups of 256 threads over the ncplx
+// The reductions below run kCnDotBlocks workgroups of 512 threads over the ncplx
 // complex entries of the vectors; each workgroup writes fixed-order partial
-// sums, and the workgroup that finishes last sums them in workgroup order
-// (bitwise reproducible) and updates `ctrl`.
+// sums, and the kernel that needs the totals sums them in a fixed order (bitwise
+// reproducible) and updates `ctrl`.
 
 // Constants of the stopping rule and the Hessenberg matrix for the calls that follow.
 hipError_t launch_cn_init(CnCtrl* ctrl, double hdt, double rtol, int max_iter, int m, hipStream_t s);
@@ -111,13 +111,13 @@ hipError_t launch_cn_rhs(const double* rx, const double* ry, double* rhs, double
 hipError_t launch_cn_residual(const double* rx, double* ry, size_t ncplx, double* partials, CnCtrl* ctrl, bool wt,
                               hipStream_t s);
 // Arnoldi iteration j (basis V, vstride doubles apart), classical Gram-Schmidt:
-// w <- wx + wy (in wx); h_k = <V_k, w> (k <= j), hn = ||w - V h||; the Givens
-// update of column j.
+// w <- wx + wy (in wx) and the partial sums of h_k = <V_k, w> (k <= j) and ||w||^2.
 hipError_t launch_cn_gs1(const double* V, size_t vstride, int j, double* wx, const double* wy, size_t ncplx,
-                         double* partials, double* rec, CnCtrl* ctrl, bool wt, hipStream_t s);
-// V_{j+1} = (w - sum h_k V_k) / hn.
-hipError_t launch_cn_gs_update(double* V, size_t vstride, int j, const double* w, size_t ncplx, const double* rec,
-                               CnCtrl* ctrl, bool wt, hipStream_t s);
+                         double* partials, bool wt, hipStream_t s);
+// V_{j+1} = (w - sum h_k V_k) / hn, hn = ||w - V h||, from those sums, and the Givens
+// update of column j.
+hipError_t launch_cn_gs_update(double* V, size_t vstride, int j, const double* w, size_t ncplx,
+                               const double* partials, double* rec, CnCtrl* ctrl, bool wt, hipStream_t s);
 // The end of a cycle (gated on ctrl->done): x += V y with R y = g solved per
 // workgroup, and the residual r = rhs - G x = V (beta e_0 - H_G y) from the
 // Arnoldi relation to r_out with its norm; then the outcome (converged, out of

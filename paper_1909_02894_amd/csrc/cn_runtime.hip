@@ -110,9 +110,8 @@ hipError_t arnoldi(const CnCtx& c, int j) {
     if (j == 0) e = apply(c, c.wy, &c.ctrl->beta, c.vec(0), 0, nullptr, 1.0, nullptr);
     else e = apply(c, c.vec(j), nullptr, nullptr, 0, nullptr, 1.0, nullptr);
     if (e != hipSuccess) return e;
-    if ((e = launch_cn_gs1(c.V, c.vstride, j, c.wx, c.wy, c.ncplx, c.part, c.rec_of(j), c.ctrl, c.wt, c.st)) != hipSuccess)
-        return e;
-    return launch_cn_gs_update(c.V, c.vstride, j, c.wx, c.ncplx, c.rec_of(j), c.ctrl, c.wt, c.st);
+    if ((e = launch_cn_gs1(c.V, c.vstride, j, c.wx, c.wy, c.ncplx, c.part, c.wt, c.st)) != hipSuccess) return e;
+    return launch_cn_gs_update(c.V, c.vstride, j, c.wx, c.ncplx, c.part, c.rec_of(j), c.ctrl, c.wt, c.st);
 }
 
 // The end of the queued iterations: the end-of-cycle kernels (the update is a
