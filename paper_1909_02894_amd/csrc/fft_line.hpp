@@ -203,9 +203,10 @@ __device__ __forceinline__ cpx<T> partner(cpx<T> v) { return {partner(v.re), par
 // 2x2 mixes (half-step exponential, directional symbol) exchange them with one
 // permlane swap (NT = 2 P L threads, half the registers per thread).
 // A line of N points is held by P = N / R logical threads.
-// TIGHT: the plain direction kernels' rule for exchanging one component at a time
-// (SEQ below); kernels with more state per thread than those keep both at once.
-template <typename T, int N, int R, int L, bool COLS, int CPT, bool TIGHT = true>
+// RULE: when components are exchanged one at a time (SEQ below): 1 the plain
+// direction kernels' rule (TIGHT), 0 that of kernels with more state per thread, which
+// keep both at once more often, 2 always.
+template <typename T, int N, int R, int L, bool COLS, int CPT, int RULE = 1>
 struct LineFFT {
     static constexpr int P = N / R;
     static constexpr int NTL = P * L;
@@ -240,8 +241,9 @@ struct LineFFT {
         return (NPASS > 1) ? (COLS ? ncomp * N * L + (ncomp * N * L / 16) * COL_PAD : L * ncomp * ROW_STRIDE) : 1;
     }
     static constexpr size_t LDS_BOTH = lds_elems(2) * sizeof(cpx<T>);
+    static constexpr bool TIGHT = RULE == 1;
     static constexpr bool SEQ =
-        CPT == 2 && (LDS_BOTH > kLdsMax ||
+        CPT == 2 && (RULE == 2 || LDS_BOTH > kLdsMax ||
                      (NT <= 256 && (LDS_BOTH > kLdsMax / 2 ||
                                     (TIGHT && LDS_BOTH > kLdsMax / 5 && N * sizeof(cpx<T>) <= kTwStageMax))));
     static constexpr int NCL = SEQ ? 1 : 2;        // components held in LDS at once
@@ -380,13 +382,20 @@ struct LineFFT {
             const int k = jj % Ns;
 #pragma unroll
             for (int r = 1; r < Rp; ++r) {
+                // RULE 2: registers are short, so a few twiddles at a time
+                if constexpr (RULE == 2) {
+                    if (r % 3 == 1) __builtin_amdgcn_sched_barrier(0);
+                }
                 const cpx<T> w = PP ? tw[tw_off(PASS) + (r - 1) * Ns + k] : tw[r * k * (N / (Ns * Rp))];
 #pragma unroll
                 for (int cc = 0; cc < NV * CPT; ++cc)
                     v[cc][t * Rp + r] = INV ? cmulc(v[cc][t * Rp + r], w) : cmul(v[cc][t * Rp + r], w);
             }
 #pragma unroll
-            for (int cc = 0; cc < NV * CPT; ++cc) dft<T, Rp, INV>(&v[cc][t * Rp]);
+            for (int cc = 0; cc < NV * CPT; ++cc) {
+                if constexpr (RULE == 2) __builtin_amdgcn_sched_barrier(0);
+                dft<T, Rp, INV>(&v[cc][t * Rp]);
+            }
         }
         if constexpr (PASS + 1 < NPASS) pass<INV, PP, PASS + 1, NB, FIRST, NV>(v, buf, c, tw);
     }
@@ -400,7 +409,10 @@ struct LineFFT {
     __device__ static __forceinline__ void fft(cpx<T> (*v)[R], cpx<T>* lds, const Coord& c,
                                                const cpx<T>* __restrict__ tw) {
 #pragma unroll
-        for (int cc = 0; cc < NV * CPT; ++cc) dft<T, R, INV>(v[cc]);
+        for (int cc = 0; cc < NV * CPT; ++cc) {
+            if constexpr (RULE == 2) __builtin_amdgcn_sched_barrier(0);
+            dft<T, R, INV>(v[cc]);
+        }
         if constexpr (NPASS > 1) pass<INV, PP, 1, NB, FIRST, NV>(v, lds, c, tw);
     }
 };

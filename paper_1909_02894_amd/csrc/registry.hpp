@@ -15,6 +15,7 @@ struct KernelEntry {
     int cpt;        // spinor components per thread (1 or 2)
     int nthreads;   // workgroup size
     const void* stage_fn[3];   // by mode: 0 flat, 1 flat + layer, 2 curved
+    const void* stream_fn[3];  // by mode: the kernel of grids with stream_from_tiles(mode) tiles, or null
     const void* obs_fn;
     int from_lines[3];         // by mode: default schedule from this many lines (negative: never)
 };
@@ -31,6 +32,7 @@ struct Registrar {
 // float), DIRAC_PREC (0/1), DIRAC_COLS (false/true), DIRAC_DIR (0/1).
 #define DIRAC_CAT2(a, b) a##b
 #define DIRAC_CAT(a, b) DIRAC_CAT2(a, b)
+#define DIRAC_STREAM(N, R, L, MODE, CPT) ::dirac::stream_fn<DIRAC_T, N, R, L, DIRAC_COLS, MODE, CPT>()
 #define DIRAC_REG_IMPL(N, R, L, CPT, OBS, FLAT, LAYER, CURVED)                                        \
     static ::dirac::Registrar DIRAC_CAT(reg_, __LINE__)(::dirac::KernelEntry{                        \
         DIRAC_PREC, N, DIRAC_DIR, R, L, CPT,                                                          \
@@ -38,6 +40,7 @@ struct Registrar {
         {reinterpret_cast<const void*>(&::dirac::stage_kernel<DIRAC_T, N, R, L, DIRAC_COLS, 0, CPT>), \
          reinterpret_cast<const void*>(&::dirac::stage_kernel<DIRAC_T, N, R, L, DIRAC_COLS, 1, CPT>), \
          reinterpret_cast<const void*>(&::dirac::stage_kernel<DIRAC_T, N, R, L, DIRAC_COLS, 2, CPT>)},\
+        {DIRAC_STREAM(N, R, L, 0, CPT), DIRAC_STREAM(N, R, L, 1, CPT), DIRAC_STREAM(N, R, L, 2, CPT)},\
         OBS, {FLAT, LAYER, CURVED}});
 // REG: a direction-kernel schedule.  REGD: one that is the default of grids with at
 // least so many lines, up to the next threshold (a negative number: never), per

@@ -446,8 +446,10 @@ Launch make_launch(const dirac_solver* s, int dir, int e_pre, int e_post, int64_
     }
     const KernelEntry* e = s->sched[dir];
     const int nlines = dir == 0 ? s->g.n2 : s->g.n1;
-    L.fn = e->stage_fn[s->curved ? 2 : (s->pml ? 1 : 0)];
-    L.grid = dim3((nlines + e->lines - 1) / e->lines);
+    const int mode = s->curved ? 2 : (s->pml ? 1 : 0), tiles = (nlines + e->lines - 1) / e->lines;
+    const bool stream = e->stream_fn[mode] && tiles >= stream_from_tiles(mode);
+    L.fn = stream ? e->stream_fn[mode] : e->stage_fn[mode];
+    L.grid = dim3(stream ? kStreamGroups : tiles);
     L.block = dim3(e->nthreads);
     if (s->prec == DIRAC_FP64) {
         auto p = stage_params<double>(s, dir, e->radix, e_pre, e_post);

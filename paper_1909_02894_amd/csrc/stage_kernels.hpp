@@ -430,6 +430,148 @@ __device__ __forceinline__ void stage_tile(const StageParams<T>& p, int tile, cp
     }
 }
 
+// Streamed column tiles.  A radix-16 tile of 64 KB per component pair leaves room for
+// one workgroup per compute unit (its registers hold 64 KB twice over), so its loads,
+// transforms and stores follow one another with nothing beside them: curved FP32 4096
+// columns ran at 1.8 TB/s with the vector units 31% and the LDS 10% busy.  One
+// workgroup per compute unit that takes several tiles in turn (stage_stream_kernel) has
+// them overlap.  Grids with fewer tiles than that, and the flat FP64 tiles (two
+// workgroups still fit: 4096 x 2048 276 us per step, streamed 300), keep a workgroup per
+// tile.  us per step, a workgroup per tile / streamed: FP32 4096^2 flat 326 / 300, layer
+// 355 / 303, curved 465 / 408; 512 x 4096 curved 60 / 55, flat 47.1 / 48.0; 256 x 4096
+// curved 41.6 / 42.5; FP32 4096 x 2048 (4 lines) curved 226 / 186; FP64 2048^2 layer
+// 176 / 159, curved 226 / 198.
+template <typename T, int N, int R, int L, bool COLS, int MODE, int CPT>
+constexpr bool stage_streams() {
+    return COLS && CPT == 2 && R == 16 && N * sizeof(cpx<T>) <= 32768 && N >= 2048 &&
+           N * L * sizeof(cpx<T>) == 65536 && (MODE != 0 || sizeof(T) == 4);
+}
+constexpr int kStreamGroups = 256;             // compute units
+// Least number of tiles for a streamed launch: one per compute unit, where the staged
+// tables already pay in the blended modes; more than that in the flat one.
+constexpr int stream_from_tiles(int mode) { return mode == 0 ? kStreamGroups + 1 : kStreamGroups; }
+
+// One workgroup takes tiles blockIdx.x, blockIdx.x + gridDim.x, ...: the loads of
+// the next tile's state are issued before this tile's transforms and arrive behind
+// them, its stores drain behind the next tile's.  Twiddles, symbols and 1/S are
+// staged in LDS once, so that no short load waits behind the long ones (loads
+// return in order); only a(x), issued first, and the call's last E are read per tile.
+// Results are bitwise those of stage_tile: every operation on a line is the same.
+template <typename T, int N, int R, int L, int MODE>
+__global__ void __launch_bounds__((N / R) * L) stage_stream_kernel(StageParams<T> p) {
+    using F = LineFFT<T, N, R, L, true, 2, 2>;
+    constexpr int P = F::P;
+    constexpr bool BLEND = MODE != 0, WIDE = sizeof(T) == 8;
+    using raw = std::conditional_t<WIDE, d2v, f4v>;
+    constexpr int RW = WIDE ? 2 : 1;
+    __shared__ cpx<T> lds[F::LDS_ELEMS];
+    __shared__ cpx<T> twl[F::TW_ENTRIES], kl[N];
+    __shared__ T sl[BLEND ? N : 1];
+    const typename F::Coord c = F::coord(threadIdx.x);
+    const uint32_t pitch = (uint32_t)p.pitch, n1 = (uint32_t)p.n1;
+    const uint32_t sln = (uint32_t)c.j * pitch + c.l, eln = (uint32_t)c.j * n1 + c.l, aln = (uint32_t)c.l * N + c.j;
+    const uint32_t sstep = P * pitch, estep = P * n1;
+    const PointAt<T, WIDE> spt(sln), ept(eln);
+    const int ntiles = p.nlines / L;           // grids are powers of two from 16 points
+    // curved tiles have no registers for the last LATE points of the next tile until
+    // this one's old values are used up (FP32 4096^2 with all 16 early: 20 registers
+    // spilled, 452 us per step, with 12: 417)
+    constexpr int LATE = MODE == 2 ? (L == 4 ? 6 : 4) : 0;
+    raw nx[R][RW];
+    auto load = [&](int tile, uint32_t sstep, int ra, int rb) {
+        const T* base = upt(p.psi, 4 * (uint32_t)tile * L);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if (r < ra || r >= rb) continue;
+            const char* q = reinterpret_cast<const char*>(upt(base, 4 * (r * sstep)));
+            if constexpr (WIDE) {
+                nx[r][0] = gld(reinterpret_cast<const d2v*>(q + spt.o.a));
+                nx[r][1] = gld(reinterpret_cast<const d2v*>(q + spt.o.b));
+            } else {
+                nx[r][0] = gld(reinterpret_cast<const f4v*>(q + spt.idx * (uint32_t)(4 * sizeof(T))));
+            }
+        }
+    };
+    int t = blockIdx.x;
+    load(xcd_tile(t, ntiles), sstep, 0, R);
+    for (int e = threadIdx.x; e < F::TW_ENTRIES; e += F::NT) twl[e] = gld(p.tw + e);
+    for (int e = threadIdx.x; e < N; e += F::NT) {
+        kl[e] = gld(p.K + e);
+        if constexpr (BLEND) sl[e] = gld(p.inv_s + e);
+    }
+    while (t < ntiles) {
+        const int tile = xcd_tile(t, ntiles);
+        cpx<T> v[2][R], old[BLEND ? 2 : 1][BLEND ? R : 1];
+        T bb[MODE == 2 ? R : 1];
+        if constexpr (MODE == 2) {
+            const T* a = upt(p.a, (uint32_t)tile * L * N);
+#pragma unroll
+            for (int r = 0; r < R; ++r) bb[r] = N >= 4096 ? ld_nt(a + r * P + aln) : ld_at(a + r * P, aln);
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if constexpr (WIDE) {
+                swap_halves(nx[r][0], nx[r][1]);
+                v[0][r] = {nx[r][0].x, nx[r][0].y};
+                v[1][r] = {nx[r][1].x, nx[r][1].y};
+            } else {
+                v[0][r] = {nx[r][0].x, nx[r][0].y};
+                v[1][r] = {nx[r][0].z, nx[r][0].w};
+            }
+            if constexpr (BLEND) {
+                old[0][r] = v[0][r];
+                old[1][r] = v[1][r];
+            }
+        }
+        t += gridDim.x;
+        // past the last tile the loads go on, to one row of the tile in hand: a branch
+        // around them costs registers on both of its sides
+        const bool more = t < ntiles;
+        const int next = more ? xcd_tile(t, ntiles) : tile;
+        const uint32_t nstep = more ? sstep : 0;
+        load(next, nstep, 0, R - LATE);
+        F::template fft<false, true>(v, lds, c, twl);
+#pragma unroll
+        for (int s = 0; s < R; ++s) {          // K_y = [[cos, -sin], [sin, cos]]
+            if (s % 4 == 0) __builtin_amdgcn_sched_barrier(0);
+            const cpx<T> k = kl[c.j + s * P], u = v[0][s], w = v[1][s];
+            v[0][s] = scal(k.re, u) - scal(k.im, w);
+            v[1][s] = scal(k.re, w) - scal(-k.im, u);
+        }
+        F::template fft<true, true>(v, lds, c, twl);
+        if constexpr (BLEND) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                if (r % 4 == 0) __builtin_amdgcn_sched_barrier(0);
+                const T sv = sl[c.j + r * P], b = MODE == 2 ? bb[r] * sv : sv;
+#pragma unroll
+                for (int cc = 0; cc < 2; ++cc) v[cc][r] = scal(b, v[cc][r]) + scal(T(1) - b, old[cc][r]);
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if (LATE > 0) load(next, nstep, R - LATE, R);
+        T* out = upt(p.psi, 4 * (uint32_t)tile * L);
+        if (p.e_post) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                if (r % 2 == 0) __builtin_amdgcn_sched_barrier(0);
+                const cpx<T> u = v[0][r], w = v[1][r];
+                if constexpr (MODE == 2) {
+                    cpx<T> e0, e1;
+                    ept.load(upt(upt(p.E, 4 * (uint32_t)tile * L), 4 * (r * estep)), e0, e1);
+                    v[0][r] = cmul(cpx<T>{e0.re, T(1) * e0.im}, u) + cmul(cpx<T>{e1.re, T(1) * e1.im}, w);
+                    v[1][r] = cmul(cpx<T>{e0.re, T(-1) * e0.im}, w) + cmul(cpx<T>{e1.re, T(-1) * e1.im}, u);
+                } else {
+                    v[0][r] = cmul(p.e0u, u);
+                    v[1][r] = cmul(cpx<T>{p.e0u.re, -p.e0u.im}, w);
+                }
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) spt.template store<false>(out, v[0][r], v[1][r], r * sstep);
+    }
+}
+
 template <typename T, int N, int R, int L, bool COLS, int MODE, int CPT>
 __global__ void __launch_bounds__((CPT == 1 ? 2 : 1) * (N / R) * L)
 stage_kernel(StageParams<T> p) {
@@ -437,6 +579,15 @@ stage_kernel(StageParams<T> p) {
     __shared__ cpx<T> lds[NB * LineFFT<T, N, R, L, COLS, CPT>::LDS_ELEMS];
     __shared__ cpx<T> twl[TwStage<T, N>::ELEMS];
     stage_tile<T, N, R, L, COLS, MODE, CPT, NB>(p, xcd_tile(blockIdx.x, gridDim.x), lds, twl);
+}
+
+// The streamed kernel of a schedule and mode, or null.
+template <typename T, int N, int R, int L, bool COLS, int MODE, int CPT>
+const void* stream_fn() {
+    if constexpr (stage_streams<T, N, R, L, COLS, MODE, CPT>())
+        return reinterpret_cast<const void*>(&stage_stream_kernel<T, N, R, L, MODE>);
+    else
+        return nullptr;
 }
 
 // Deterministic workgroup sum of NV doubles per thread into out[0..NV).

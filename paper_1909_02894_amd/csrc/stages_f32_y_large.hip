@@ -19,7 +19,7 @@ REGD(1024, 16, 4, 2, 2048, 2048, 2048)
 REGD(2048, 16, 2, 2, 512, 512, 512)
 REGOD(2048, 8, 2, 2, 0, 0, 0)
 REG(2048, 16, 4, 1)
-REG(2048, 16, 4, 2)
+REGD(2048, 16, 4, 2, -1, 2048, 2048)
 REGOD(4096, 16, 2, 2, 0, 0, 0)
 REG(4096, 16, 2, 1)
 REG(4096, 8, 2, 2)

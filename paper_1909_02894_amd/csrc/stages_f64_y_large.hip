@@ -17,10 +17,10 @@ REGOD(1024, 8, 4, 2, -1, 1024, -1)
 REGD(1024, 8, 4, 1, 1024, -1, -1)
 REGD(1024, 8, 2, 2, 2048, 2048, 1024)
 REGD(1024, 8, 2, 1, 0, 0, 0)
-REGOD(2048, 8, 2, 2, -1, 512, -1)
+REGO(2048, 8, 2, 2)
 REGD(2048, 8, 1, 2, 0, 0, 0)
 REGD(2048, 8, 2, 1, 256, -1, -1)
-REGD(2048, 16, 2, 2, 1024, -1, 512)
+REGD(2048, 16, 2, 2, 1024, 512, 512)
 REGO(4096, 8, 1, 2)
 REGD(4096, 8, 1, 1, 0, 0, 0)
 REG(4096, 8, 2, 2)
