@@ -63,6 +63,11 @@ __host__ __device__ constexpr bool bsched_valid(int n, int s) {
            n % (bsched_radix(n, s) * bsched_radix(n, s)) == 0;
 }
 __host__ __device__ constexpr int bsched_lines(int n, int s) { return kBatchThreads / bsched_threads_per_line(n, s); }
+// LineFFT's rule for exchanging components one at a time: not at 128 points and below,
+// whose batches are short of workgroups rather than of LDS (us per step, one at a time /
+// both: 7 solves of 128^2 16.3 / 16.1, of 64 to 128 16.7 / 16.4; 64 of 128 to 512 keep
+// it above 128: 207 against 219 with both everywhere).
+__host__ __device__ constexpr int bsched_rule(int n) { return n <= 128 ? 0 : 1; }
 __host__ __device__ constexpr int batch_lines(int n) { return bsched_lines(n, 0); }
 
 constexpr int kBatchMaxGroups = 8;
@@ -86,7 +91,7 @@ struct BatchMultiPhase {
 
 template <typename T, bool COLS, int N, int S>
 __host__ __device__ constexpr size_t batch_smem_bytes_s() {
-    return (LineFFT<T, N, bsched_radix(N, S), bsched_lines(N, S), COLS, bsched_cpt(S)>::LDS_ELEMS +
+    return (LineFFT<T, N, bsched_radix(N, S), bsched_lines(N, S), COLS, bsched_cpt(S), bsched_rule(N)>::LDS_ELEMS +
             TwStage<T, N>::ELEMS) * sizeof(cpx<T>);
 }
 template <typename T, bool COLS, int N>
@@ -97,7 +102,7 @@ __host__ __device__ constexpr size_t batch_smem_bytes() {
 template <typename T, bool COLS, int N, int S>
 __device__ __forceinline__ void batch_tile(const BatchDesc<T>& d, int tile, int k, char* smem) {
     constexpr int R = bsched_radix(N, S), L = bsched_lines(N, S), CPT = bsched_cpt(S);
-    using F = LineFFT<T, N, R, L, COLS, CPT>;
+    using F = LineFFT<T, N, R, L, COLS, CPT, bsched_rule(N)>;
     static_assert(F::NT == kBatchThreads, "batch schedules use 256-thread workgroups");
     cpx<T>* lds = reinterpret_cast<cpx<T>*>(smem);
     cpx<T>* twl = lds + F::LDS_ELEMS;
@@ -116,9 +121,9 @@ __device__ __forceinline__ void batch_tile(const BatchDesc<T>& d, int tile, int 
     p.e_post = COLS ? (k == d.steps - 1 ? 1 : 0) : 0;
     p.e0u = d.e0u;
     p.wt = 0;
-    if (d.mode == 0) stage_tile<T, N, R, L, COLS, 0, CPT>(p, tile, lds, twl);
-    else if (d.mode == 1) stage_tile<T, N, R, L, COLS, 1, CPT>(p, tile, lds, twl);
-    else stage_tile<T, N, R, L, COLS, 2, CPT>(p, tile, lds, twl);
+    if (d.mode == 0) stage_tile<T, N, R, L, COLS, 0, CPT, 1, bsched_rule(N)>(p, tile, lds, twl);
+    else if (d.mode == 1) stage_tile<T, N, R, L, COLS, 1, CPT, 1, bsched_rule(N)>(p, tile, lds, twl);
+    else stage_tile<T, N, R, L, COLS, 2, CPT, 1, bsched_rule(N)>(p, tile, lds, twl);
 }
 
 // Phase kernel of one size group: the workgroup -> (solve, tile) map is a

@@ -243,9 +243,9 @@ constexpr int stage_buffers() {
 // the 2x2 mixes are written per output component as (own, other) expressions
 // that are the same whether the other component sits in the same thread
 // (CPT = 2) or in the partner lane (CPT = 1), so results do not depend on L or CPT.
-template <typename T, int N, int R, int L, bool COLS, int MODE, int CPT, int NB = 1>
+template <typename T, int N, int R, int L, bool COLS, int MODE, int CPT, int NB = 1, int RULE = 1>
 __device__ __forceinline__ void stage_tile(const StageParams<T>& p, int tile, cpx<T>* lds, cpx<T>* twl) {
-    using F = LineFFT<T, N, R, L, COLS, CPT>;
+    using F = LineFFT<T, N, R, L, COLS, CPT, RULE>;
     using TS = TwStage<T, N>;
     constexpr int P = F::P;
     constexpr bool BLEND = MODE != 0;
