@@ -81,22 +81,30 @@ __device__ __forceinline__ T gld(const T* p) { return *(const __attribute__((add
 template <typename T>
 __device__ __forceinline__ void gst(T* p, T v) { *(__attribute__((address_space(1))) T*)p = v; }
 // Device-scope write-through stores (buffer_store ... sc1) of 16 or 8 bytes at
-// byte offset `off` + `uoff` (uoff wave-uniform) from the wave-uniform `base`: the line goes to memory at
+// byte offset `off` from the wave-uniform `base`: the line goes to memory at
 // once instead of sitting dirty in this XCD's L2 until the end-of-dispatch
 // write-back.  Full-width stores, so a wave's contiguous stores still combine
 // into whole lines.  The resource's third dword is the gfx9 raw-buffer format;
 // the range (2 GiB) covers every supported state.
+// A wave-uniform part of the address belongs in `base`, never in the scalar
+// offset: a 16-byte store reads its data after it has issued, and behind a register
+// as scalar offset the compiler does not keep the two wait states before a VALU
+// instruction may write that data again (it does behind a constant).  With r * step
+// there, the FP64 tiles whose next half-wave swap starts in the store's own
+// registers (two components per thread) had a v_mov into the first of them, the low
+// word of a double, in the very next slot: curved FP64 4096 x 32 rows ended 1e-9
+// from the reference, in some runs only.
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t wt_rsrc(const void* base) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, 0x7fffffff, 0x00020000);
 }
 constexpr int kCacheSc1 = 16;      // cache-policy bit sc1 of the buffer intrinsics
-__device__ __forceinline__ void gst_wt16(const void* base, uint32_t off, u32x4 v, uint32_t uoff = 0) {
-    __builtin_amdgcn_raw_buffer_store_b128(v, wt_rsrc(base), (int)off, (int)uoff, kCacheSc1);
+__device__ __forceinline__ void gst_wt16(const void* base, uint32_t off, u32x4 v) {
+    __builtin_amdgcn_raw_buffer_store_b128(v, wt_rsrc(base), (int)off, 0, kCacheSc1);
 }
-__device__ __forceinline__ void gst_wt8(const void* base, uint32_t off, u32x2 v, uint32_t uoff = 0) {
-    __builtin_amdgcn_raw_buffer_store_b64(v, wt_rsrc(base), (int)off, (int)uoff, kCacheSc1);
+__device__ __forceinline__ void gst_wt8(const void* base, uint32_t off, u32x2 v) {
+    __builtin_amdgcn_raw_buffer_store_b64(v, wt_rsrc(base), (int)off, 0, kCacheSc1);
 }
 __device__ __forceinline__ cpx<float> gld(const cpx<float>* p) {
     const f2v v = gld(reinterpret_cast<const f2v*>(p));

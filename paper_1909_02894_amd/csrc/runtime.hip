@@ -301,9 +301,11 @@ bool pick_store_mode(int prec, int n, int dir, int other, int mode) {
     // The corrected second-order step's columns beyond 512 points are one-line
     // tiles with both components per thread (FP32 1024^2 49.3 / 54.8).
     if ((mode & 4) && dir == 1 && n > 512) return false;
-    // Rows of 4096 points and more keep ordinary stores: curved FP64 4096 x 32, written
-    // through, ended 1e-9 from the reference in three of five runs of one test order
-    // (ordinary stores: none), with no cause found; 4096 x 512 FP32 gives up the 49.7.
+    // Rows of 4096 points and more keep ordinary stores: they were taken out of this rule
+    // while the missing wait behind these stores was looked for (gst_wt16), and have not
+    // been put back.  Written through they would gain (us per step, ordinary / both
+    // directions): curved FP32 4096 x 512 42.5 / 39.3, 4096 x 128 25.1 / 18.8, FP64 4096 x 32
+    // 24.2 / 21.4, 4096 x 256 47.3 / 45.3.
     if ((dir == 0 ? n : other) >= kPadFromN1) return false;
     if (dir == 0) return bytes <= size_t(32) << 20;
     return bytes <= size_t(prec == DIRAC_FP32 ? 32 : 16) << 20 && (n <= 256 || other >= 256);

@@ -132,11 +132,12 @@ template <bool WT = false>
 __device__ __forceinline__ void store_points(double* p, PairOffsets o, cpx<double> u, cpx<double> v, uint32_t uidx = 0) {
     d2v A{u.re, u.im}, B{v.re, v.im};
     swap_halves(A, B);
+    p = upt(p, 4 * uidx);
     if constexpr (WT) {
-        gst_wt16(p, o.a, __builtin_bit_cast(u32x4, A), uidx * 32);
-        gst_wt16(p, o.b, __builtin_bit_cast(u32x4, B), uidx * 32);
+        gst_wt16(p, o.a, __builtin_bit_cast(u32x4, A));
+        gst_wt16(p, o.b, __builtin_bit_cast(u32x4, B));
     } else {
-        char* c = reinterpret_cast<char*>(upt(p, 4 * uidx));
+        char* c = reinterpret_cast<char*>(p);
         gst(reinterpret_cast<d2v*>(c + o.a), A);
         gst(reinterpret_cast<d2v*>(c + o.b), B);
     }
@@ -172,35 +173,36 @@ constexpr int kStoreWtMaxColN = 1024;
 // The point is idx + uidx (uidx wave-uniform).
 template <typename T, bool WT = false>
 __device__ __forceinline__ void store_point(T* p, uint32_t idx, cpx<T> u, cpx<T> v, uint32_t uidx = 0) {
-    const uint32_t off = idx * (uint32_t)(4 * sizeof(T)), uoff = uidx * (uint32_t)(4 * sizeof(T));
-    char* b = reinterpret_cast<char*>(upt(p, 4 * uidx)) + off;
+    const uint32_t off = idx * (uint32_t)(4 * sizeof(T));
+    p = upt(p, 4 * uidx);
+    char* b = reinterpret_cast<char*>(p) + off;
     if constexpr (sizeof(T) == 8) {
         const d2v a{u.re, u.im}, c{v.re, v.im};
         if constexpr (WT) {
-            gst_wt16(p, off, __builtin_bit_cast(u32x4, a), uoff);
-            gst_wt16(p, off + 16, __builtin_bit_cast(u32x4, c), uoff);
+            gst_wt16(p, off, __builtin_bit_cast(u32x4, a));
+            gst_wt16(p, off + 16, __builtin_bit_cast(u32x4, c));
         } else {
             gst(reinterpret_cast<d2v*>(b), a);
             gst(reinterpret_cast<d2v*>(b) + 1, c);
         }
     } else {
         const f4v a{u.re, u.im, v.re, v.im};
-        if constexpr (WT) gst_wt16(p, off, __builtin_bit_cast(u32x4, a), uoff);
+        if constexpr (WT) gst_wt16(p, off, __builtin_bit_cast(u32x4, a));
         else gst(reinterpret_cast<f4v*>(b), a);
     }
 }
 template <typename T, bool WT = false>
 __device__ __forceinline__ void store_comp(T* p, uint32_t idx, int c, cpx<T> v, uint32_t uidx = 0) {
     const uint32_t off = idx * (uint32_t)(4 * sizeof(T)) + c * (uint32_t)(2 * sizeof(T));
-    const uint32_t uoff = uidx * (uint32_t)(4 * sizeof(T));
-    char* b = reinterpret_cast<char*>(upt(p, 4 * uidx)) + off;
+    p = upt(p, 4 * uidx);
+    char* b = reinterpret_cast<char*>(p) + off;
     if constexpr (sizeof(T) == 8) {
         const d2v a{v.re, v.im};
-        if constexpr (WT) gst_wt16(p, off, __builtin_bit_cast(u32x4, a), uoff);
+        if constexpr (WT) gst_wt16(p, off, __builtin_bit_cast(u32x4, a));
         else gst(reinterpret_cast<d2v*>(b), a);
     } else {
         const f2v a{v.re, v.im};
-        if constexpr (WT) gst_wt8(p, off, __builtin_bit_cast(u32x2, a), uoff);
+        if constexpr (WT) gst_wt8(p, off, __builtin_bit_cast(u32x2, a));
         else gst(reinterpret_cast<f2v*>(b), a);
     }
 }
