@@ -279,7 +279,10 @@ int tune_mode(const dirac_solver* s) {
 
 // Whether the direction kernel carries the write-through store path (every
 // row kernel; column kernels up to kStoreWtMaxColN points, stage_tile).
-bool store_wt_compiled(const dirac_solver* s, int dir) { return dir == 0 || s->g.n2 <= kStoreWtMaxColN; }
+// Scheme I has no direction kernel.
+bool store_wt_compiled(const dirac_solver* s, int dir) {
+    return s->scheme.scheme != DIRAC_SCHEME_CN_GMRES && (dir == 0 || s->g.n2 <= kStoreWtMaxColN);
+}
 
 // Store mode the autotuner measured fastest for this direction and shape, else
 // by size.

@@ -1,0 +1,76 @@
+"""Host-side decisions of the built library on the CPU: a child process loads it
+with tests/hostcheck/hipstub.cpp in place of the HIP runtime ("device" memory is host
+memory, no kernel runs) and tests/hostcheck/inject.cpp, which records launches and can
+make an event wait fail."""
+import os
+import shutil
+import subprocess
+import sys
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HERE = os.path.join(ROOT, "tests", "hostcheck")
+
+PRELUDE = """
+import ctypes as C
+import sys
+import numpy as np
+stub = C.CDLL(sys.argv[1], mode=C.RTLD_GLOBAL)      # before the library: its HIP calls resolve here
+from paper_1909_02894_amd import dirac as D
+stub.inject_launch_fn.restype = C.c_void_p
+stub.inject_launch_grid.restype = C.c_uint
+
+
+def solver(n1, n2, prec=0, kind="curved", scheme=0, pml=None):
+    pml = (0 if kind == "flat" else 2) if pml is None else pml
+    g, m, p, _ = D.make_structs(n1, n2, 20.0, 20.0, 1e-4, 1.0, 0.5, metric=0 if kind != "curved" else 1,
+                                spin=0 if kind != "curved" else 2, bump_A=1.0, bump_s=3.0, pml_width=pml)
+    sc = D.Scheme(scheme, 0, 0, 0, 0.0)
+    nb = D.footprint_bytes_ex(g, m, p, prec, sc, None)
+    buf = np.zeros(nb, np.uint8)
+    h = D.create_solver(g, m, p, prec, sc, None, buf.ctypes.data, nb, None)
+    D.set_initial_spinor(h, np.zeros((n2, n1, 2), np.complex128))
+    return h, buf
+
+
+def store_mode(h):
+    v = C.c_int32(-1)
+    assert D.lib.dirac_get_store_mode(h, C.byref(v)) == 0
+    return v.value
+
+
+def schedule(h, d):
+    s = D.Schedule()
+    assert D.lib.dirac_get_schedule(h, d, C.byref(s)) == 0
+    return s.radix, s.lines_per_wg, s.components_per_thread
+"""
+
+
+@pytest.fixture(scope="module")
+def run(tmp_path_factory):
+    if not (shutil.which("g++") and os.path.isdir("/opt/rocm/include/hip")):
+        pytest.skip("no toolchain")
+    lib = str(tmp_path_factory.mktemp("stub") / "libstub.so")
+    cc = ["g++", "-shared", "-fPIC", "-O1", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-w"]
+    objs = []
+    for f, extra in (("hipstub.cpp", ["-DhipLaunchKernel=stub_hipLaunchKernel",
+                                      "-DhipEventSynchronize=stub_hipEventSynchronize"]), ("inject.cpp", [])):
+        objs.append(lib + "." + f + ".o")
+        subprocess.run([*cc, *extra, "-c", os.path.join(HERE, f), "-o", objs[-1]], check=True)
+    subprocess.run([*cc, *objs, "-o", lib], check=True)
+
+    def child(script):
+        r = subprocess.run([sys.executable, "-c", PRELUDE + script, lib], cwd=ROOT, capture_output=True,
+                           text=True, timeout=300)
+        assert r.returncode == 0, (r.stdout[-2000:], r.stderr[-3000:])
+    return child
+
+
+def test_scheme1_has_no_store_mode(run):
+    # the mask that dirac_set_store_mode refuses for Scheme I is not reported either
+    run("""
+h, buf = solver(64, 64, scheme=D.SCHEME_CN_GMRES)
+assert store_mode(h) == 0, store_mode(h)
+assert D.lib.dirac_set_store_mode(h, 1) == -1
+""")
