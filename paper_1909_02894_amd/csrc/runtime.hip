@@ -1240,6 +1240,8 @@ dirac_status dirac_autotune(dirac_solver* s, int32_t reps) {
         hipEventElapsedTime(&ms, e0, e1);
         return DIRAC_OK;
     };
+    const KernelEntry* sched0[2] = {s->sched[0], s->sched[1]};
+    const bool wt0[2] = {s->store_wt[0], s->store_wt[1]};
     // Coordinate search over (schedule, store mode) per direction, two sweeps
     // x, y, x, y: the choices interact (the y kernel reads what the x kernel
     // wrote, and how it was written), so each direction is re-tuned once with
@@ -1269,8 +1271,12 @@ dirac_status dirac_autotune(dirac_solver* s, int32_t reps) {
             dir_ms[dir] = best_ms;
         }
     }
-    if (result != DIRAC_OK) s->store_wt[0] = s->store_wt[1] = false;
-    if (result == DIRAC_OK) {
+    if (result != DIRAC_OK) {                       // the choices it found
+        for (int dir = 0; dir < 2; ++dir) {
+            s->sched[dir] = sched0[dir];
+            s->store_wt[dir] = wt0[dir];
+        }
+    } else {
         std::lock_guard<std::mutex> lk(tune_mutex());
         for (int dir = 0; dir < 2; ++dir) {
             const int n = dir == 0 ? s->g.n1 : s->g.n2;

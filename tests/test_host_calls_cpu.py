@@ -74,3 +74,23 @@ h, buf = solver(64, 64, scheme=D.SCHEME_CN_GMRES)
 assert store_mode(h) == 0, store_mode(h)
 assert D.lib.dirac_set_store_mode(h, 1) == -1
 """)
+
+
+@pytest.mark.parametrize("waits", [0, 3, 9])
+def test_failed_tuning_leaves_the_solver_as_it_was(run, waits):
+    run(f"""
+for kind, chosen in (("curved", None), ("flat", (1, (8, 1, 1), (8, 4, 1)))):
+    h, buf = solver(256, 128, kind=kind)
+    assert store_mode(h) == 3
+    if chosen:
+        assert D.lib.dirac_set_store_mode(h, chosen[0]) == 0
+        for d in (0, 1):
+            s = D.Schedule(*chosen[1 + d])
+            assert D.lib.dirac_set_schedule(h, d, C.byref(s)) == 0
+    before = store_mode(h), schedule(h, 0), schedule(h, 1)
+    stub.inject_failing_wait({waits})
+    assert D.lib.dirac_autotune(h, 2) == -5
+    stub.inject_failing_wait(-1)
+    assert (store_mode(h), schedule(h, 0), schedule(h, 1)) == before, (before, store_mode(h), schedule(h, 0))
+    assert D.lib.dirac_autotune(h, 2) == 0
+""")
