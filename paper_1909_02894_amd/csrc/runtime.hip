@@ -659,8 +659,9 @@ dirac_status dirac_create_solver(const dirac_grid* g, const dirac_metric* m, con
     if (bytes < lay.total)
         return fail(DIRAC_E_SIZE, "device buffer of %zu bytes < footprint %zu", bytes, lay.total);
     for (int dir = 0; dir < 2; ++dir) {
-        const int n = dir == 0 ? g->n1 : g->n2;
-        if (!obs_entry(prec, n, dir))
+        const int n = dir == 0 ? g->n1 : g->n2, nlines = dir == 0 ? g->n2 : g->n1;
+        const int mode = m->kind != DIRAC_METRIC_FLAT ? 2 : (pml->width_pts > 0 ? 1 : 0);
+        if (!default_entry(prec, n, dir, nlines, mode) || !obs_entry(prec, n, dir))
             return fail(DIRAC_E_SIZE, "no compiled kernel for n = %d (precision %d, direction %d)", n, prec, dir);
     }
     // Check the pointer is device memory of the current device.

@@ -94,3 +94,23 @@ for kind, chosen in (("curved", None), ("flat", (1, (8, 1, 1), (8, 4, 1)))):
     assert (store_mode(h), schedule(h, 0), schedule(h, 1)) == before, (before, store_mode(h), schedule(h, 0))
     assert D.lib.dirac_autotune(h, 2) == 0
 """)
+
+
+def test_every_shape_has_a_default_schedule(run):
+    # each length, direction, mode and precision from 16 lines on, through the line
+    # counts where the defaults change; what is chosen is one of the compiled schedules
+    run("""
+for prec, top in ((0, 4096), (1, 8192)):
+    for n in (16, 32, 64, 128, 256, 512, 1024, 2048, 4096, 8192):
+        for other in (16, 64, 256):
+            for d in (0, 1):
+                n1, n2 = (n, other) if d == 0 else (other, n)
+                for kind in ("flat", "layer", "curved"):
+                    if n > top:
+                        continue
+                    h, buf = solver(n1, n2, prec, kind)
+                    for dd, ln in ((0, n1), (1, n2)):
+                        assert schedule(h, dd) in D.schedules(ln, prec, dd)
+                    D.step_n(h, 1)
+                    assert D.lib.dirac_destroy(h) == 0
+""")
