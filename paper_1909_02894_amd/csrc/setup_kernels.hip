@@ -265,11 +265,12 @@ __global__ void f32_to_c128_kernel(const float* src, double* dst, size_t count) 
 }
 
 // Rows of 2^lg pairs of reals between two row pitches (in reals; both even).
-// Bound by memory: 4096^2 FP32 rows widened in 0.2 ms against the ~10 ms of
-// their download.
+// The source may be a caller's array, aligned to its elements only; the destination
+// is the solver's.  Bound by memory: 4096^2 FP32 rows widened in 0.2 ms against the
+// ~10 ms of their download.
 template <typename S, typename D>
 __global__ void copy_rows_kernel(const S* src, size_t spitch, D* dst, size_t dpitch, int lg, size_t pairs) {
-    struct alignas(2 * sizeof(S)) S2 { S a, b; };
+    struct S2 { S a, b; };
     struct alignas(2 * sizeof(D)) D2 { D a, b; };
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < pairs; i += (size_t)gridDim.x * blockDim.x) {
         const size_t row = i >> lg, col = 2 * (i & (((size_t)1 << lg) - 1));
