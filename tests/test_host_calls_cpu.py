@@ -114,3 +114,34 @@ for prec, top in ((0, 4096), (1, 8192)):
                     D.step_n(h, 1)
                     assert D.lib.dirac_destroy(h) == 0
 """)
+
+
+def test_which_column_launches_stream(run):
+    # a streamed launch has 256 workgroups and a kernel of its own; below its least tile
+    # count (256, flat 257) and for flat FP64 the same schedule launches a workgroup per tile
+    run("""
+def column_launch(n1, n2, prec, kind, sy):
+    h, buf = solver(n1, n2, prec, kind)
+    s = D.Schedule(*sy)
+    assert D.lib.dirac_set_schedule(h, 1, C.byref(s)) == 0
+    D.step_n(h, 1)                       # the x launch, then the y launch
+    r = stub.inject_launch_fn(1), stub.inject_launch_grid(1)
+    assert D.lib.dirac_destroy(h) == 0
+    return r
+
+
+cases = [(0, 2048, (16, 2, 2), 512, {"layer": True, "curved": True, "flat": False}),
+         (0, 2048, (16, 2, 2), 1024, {"layer": True, "curved": True, "flat": False}),
+         (1, 4096, (16, 2, 2), 512, {"layer": True, "curved": True, "flat": False}),
+         (1, 4096, (16, 2, 2), 1024, {"layer": True, "curved": True, "flat": True}),
+         (1, 2048, (16, 4, 2), 1024, {"layer": True, "curved": True, "flat": False}),
+         (1, 2048, (16, 4, 2), 2048, {"layer": True, "curved": True, "flat": True}),
+         (1, 4096, (16, 2, 1), 1024, {"layer": False, "curved": False, "flat": False}),
+         (1, 2048, (16, 4, 1), 2048, {"layer": False, "curved": False, "flat": False})]
+for prec, n2, sy, n1, modes in cases:
+    for kind, streams in modes.items():
+        plain = column_launch(n1 // 4, n2, prec, kind, sy)
+        assert plain[1] == n1 // 4 // sy[1]
+        fn, grid = column_launch(n1, n2, prec, kind, sy)
+        assert (fn != plain[0]) == streams and grid == (256 if streams else n1 // sy[1]), (prec, n1, n2, kind, grid)
+""")
