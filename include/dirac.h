@@ -296,10 +296,13 @@ dirac_status dirac_set_schedule(dirac_solver* s, int32_t direction, const dirac_
  * bit 1 for the y kernel; a set bit selects device-scope write-through stores,
  * which send each line to memory at once instead of leaving it dirty in the
  * XCD's L2 until the kernel ends (0 = ordinary stores).  Write-through pays on
- * small grids whose kernels are latency-bound and loses on large streaming ones:
- * the default goes by the state's size (up to 32 MB, FP64 columns 16 MB);
- * dirac_autotune measures both per direction and keeps the faster.  Results are bitwise the same either way.  Every form
- * of Scheme II's directional step (not Scheme I); write-through for the y
+ * small grids whose kernels are latency-bound and loses on large streaming ones.
+ * The default is write-through for states up to 32 MB (the FP64 y kernel: 16 MB), but
+ * ordinary stores for both kernels of grids with n1 >= 4096, and for the y kernel of
+ * n2 > 256 with n1 < 256 and of the corrected second-order step with n2 > 512;
+ * dirac_get_store_mode tells which.  dirac_autotune measures both per direction and
+ * keeps the faster.  Results are bitwise the same either way.  Every form of
+ * Scheme II's directional step (Scheme I: always 0); write-through for the y
  * kernel only with n2 <= 1024 (else DIRAC_E_ARG). */
 dirac_status dirac_set_store_mode(dirac_solver* s, int32_t write_through);
 dirac_status dirac_get_store_mode(const dirac_solver* s, int32_t* write_through);

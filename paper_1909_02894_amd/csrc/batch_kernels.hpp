@@ -67,7 +67,7 @@ __host__ __device__ constexpr int bsched_lines(int n, int s) { return kBatchThre
 // whose batches are short of workgroups rather than of LDS (us per step, one at a time /
 // both: 7 solves of 128^2 16.3 / 16.1, of 64 to 128 16.7 / 16.4; 64 of 128 to 512 keep
 // it above 128: 207 against 219 with both everywhere).
-__host__ __device__ constexpr int bsched_rule(int n) { return n <= 128 ? 0 : 1; }
+__host__ __device__ constexpr int bsched_rule(int n) { return n <= 128 ? kSeqLoose : kSeqTight; }
 __host__ __device__ constexpr int batch_lines(int n) { return bsched_lines(n, 0); }
 
 constexpr int kBatchMaxGroups = 8;

@@ -50,7 +50,7 @@ const BisEntry* bis_entry(int prec, int n, int dir, int nlines);
 template <typename T, int N, int L, int CPT, bool COLS, int MODE>
 __global__ void __launch_bounds__(bis_threads(N, L, CPT)) bis_stage_kernel(BisParams<T> bp) {
     constexpr int R = kBisRadix;
-    using F = LineFFT<T, N, R, L, COLS, CPT, false>;
+    using F = LineFFT<T, N, R, L, COLS, CPT, kSeqLoose>;
     using TS = TwStage<T, N>;
     constexpr int P = F::P;
     constexpr int dir = COLS ? 1 : 0;

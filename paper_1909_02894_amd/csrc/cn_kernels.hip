@@ -9,10 +9,12 @@
 // Gram-Schmidt pass does not cancel and keeps the basis orthonormal to rounding
 // over a cycle (on G = I + (dt/2) A almost all of G v lies along v and one pass
 // loses orthogonality completely).  The Hessenberg matrix of G is
-// I + (dt/2) H_A.  Each reduction ends in one workgroup that sums the
-// per-workgroup partials in a fixed order (bitwise reproducible) and updates the
-// device-resident least-squares state (Givens rotations), so a whole GMRES cycle
-// needs no host round trip.
+// I + (dt/2) H_A.  The kernel that needs a reduction's totals sums the per-workgroup
+// partials itself, in a fixed order (bitwise reproducible): every workgroup of the
+// Gram-Schmidt update, one of which also updates the device-resident least-squares
+// state (Givens rotations), and after a residual a finishing kernel of one workgroup.
+// So a whole GMRES cycle needs no host round trip; a step of j iterations on a square
+// grid up to 512 points is 8 + 3 j launches (up to 8 basis vectors per reduction).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -48,7 +50,7 @@ template <int N, bool COLS, bool M2 = false>
 struct CnTile {
     static constexpr int R = M2 ? cn2_radix(N) : cn_radix(N, COLS), L = M2 ? cn2_lines(N) : cn_lines(N, COLS);
     static constexpr int CPT = M2 ? kCn2Cpt : cn_cpt(COLS);
-    using F = LineFFT<double, N, R, L, COLS, CPT, false>;
+    using F = LineFFT<double, N, R, L, COLS, CPT, kSeqLoose>;
     static constexpr int NT = F::NT;
     static constexpr int LDS = F::LDS_ELEMS;
     static constexpr int TW = TwStage<double, N>::ELEMS;
@@ -608,7 +610,7 @@ __device__ void finish_column(const double* partials, int j, double* rec, CnCtrl
 // own between the two kernels held the chip for 4.7 us and a launch gap per
 // iteration (512^2: 209 -> 199 us per step).  256 workgroups of 512 threads keep
 // what each must sum small (512 of 512: 208 us, 512 of 256: 200, and 2048^2
-// 4212 / 4291 / 4248).
+// 4212 / 4291 / 4248); the Givens workgroup is one more, number 0, which updates nothing.
 template <int NKR>
 __global__ void __launch_bounds__(kCnThreads) cn_gs_update_kernel(double* V, size_t vstride, int nfull, int j,
                                                                    const double* w, size_t ncplx,

@@ -14,8 +14,9 @@ constexpr int kCnChunk = 8;           // basis vectors one reduction launch hand
 
 // Device-resident state of the GMRES solve of one step: the Hessenberg
 // least-squares problem after Givens rotations (R, cs, sn, g), the cycle's
-// counters and the stopping rule.  Written by the single-workgroup finish
-// kernels (and the init kernel) and read by the other kernels.
+// counters and the stopping rule.  Written by one workgroup at a time (the finish
+// kernel's, workgroup 0 of the Gram-Schmidt update, the init kernel's) and read by
+// the other kernels.
 struct CnCtrl {
     // head (CnHead): the fields the host reads after a cycle
     double beta;          // norm of the current cycle's starting residual

@@ -79,7 +79,7 @@ template <typename T, int N, int DIR, int MODE>
 __global__ void __launch_bounds__(d3_threads<T>(N)) d3_stage_kernel(D3Params<T> p) {
     constexpr int R = d3_radix<T>(N), L = d3_lines<T>(N);
     constexpr bool COLS = DIR != 0, BLEND = MODE != 0, PRELOAD_E = MODE == 2 && DIR == 0;
-    using F = LineFFT<T, N, R, L, COLS, 2, false>;
+    using F = LineFFT<T, N, R, L, COLS, 2, kSeqLoose>;
     using TS = TwStage<T, N>;
     static_assert(F::NT % 32 == 0 && !F::SEQ, "whole half-waves, both components exchanged at once");
     constexpr int P = F::P;

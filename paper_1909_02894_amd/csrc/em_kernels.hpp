@@ -150,7 +150,7 @@ __device__ __forceinline__ void apply_mat(const Mat2& m, cpx<T>& u, cpx<T>& v) {
 template <typename T, int N, bool COLS>
 __global__ void __launch_bounds__(em_threads(N, COLS)) em_stage_kernel(EmParams<T> ep) {
     constexpr int R = em_radix(N), L = em_lines(N, COLS);
-    using F = LineFFT<T, N, R, L, COLS, 2, false>;
+    using F = LineFFT<T, N, R, L, COLS, 2, kSeqLoose>;
     using TS = TwStage<T, N>;
     constexpr int P = F::P;
     __shared__ cpx<T> lds[F::LDS_ELEMS];

@@ -211,10 +211,11 @@ __device__ __forceinline__ cpx<T> partner(cpx<T> v) { return {partner(v.re), par
 // 2x2 mixes (half-step exponential, directional symbol) exchange them with one
 // permlane swap (NT = 2 P L threads, half the registers per thread).
 // A line of N points is held by P = N / R logical threads.
-// RULE: when components are exchanged one at a time (SEQ below): 1 the plain
-// direction kernels' rule (TIGHT), 0 that of kernels with more state per thread, which
-// keep both at once more often, 2 always.
-template <typename T, int N, int R, int L, bool COLS, int CPT, int RULE = 1>
+// RULE: when components are exchanged one at a time (SEQ below): kSeqTight the plain
+// direction kernels' rule, kSeqLoose that of kernels with more state per thread, which
+// keep both at once more often, kSeqAlways every time.
+constexpr int kSeqLoose = 0, kSeqTight = 1, kSeqAlways = 2;
+template <typename T, int N, int R, int L, bool COLS, int CPT, int RULE = kSeqTight>
 struct LineFFT {
     static constexpr int P = N / R;
     static constexpr int NTL = P * L;
@@ -241,7 +242,7 @@ struct LineFFT {
     // from memory keep both at once up to 80 KB (curved FP64 2048 rows 100 / 181:
     // the registers spill), and so do larger workgroups (FP32 4096 columns,
     // radix 16 x 2 lines of 512 threads: 269 / 391, nothing more fits beside them).
-    // Not TIGHT: flat FP32 3-D 256 x 256 x 128 300 / 319 us per step, corrected
+    // kSeqLoose: flat FP32 3-D 256 x 256 x 128 300 / 319 us per step, corrected
     // second-order FP64 1024^2 87.5 / 89.6.
     static constexpr int ROW_STRIDE = N + N / R;
     static constexpr int COL_PAD = (L == 1 || R >= 16) ? 1 : 16 / R;
@@ -249,11 +250,10 @@ struct LineFFT {
         return (NPASS > 1) ? (COLS ? ncomp * N * L + (ncomp * N * L / 16) * COL_PAD : L * ncomp * ROW_STRIDE) : 1;
     }
     static constexpr size_t LDS_BOTH = lds_elems(2) * sizeof(cpx<T>);
-    static constexpr bool TIGHT = RULE == 1;
     static constexpr bool SEQ =
-        CPT == 2 && (RULE == 2 || LDS_BOTH > kLdsMax ||
+        CPT == 2 && (RULE == kSeqAlways || LDS_BOTH > kLdsMax ||
                      (NT <= 256 && (LDS_BOTH > kLdsMax / 2 ||
-                                    (TIGHT && LDS_BOTH > kLdsMax / 5 && N * sizeof(cpx<T>) <= kTwStageMax))));
+                                    (RULE == kSeqTight && LDS_BOTH > kLdsMax / 5 && N * sizeof(cpx<T>) <= kTwStageMax))));
     static constexpr int NCL = SEQ ? 1 : 2;        // components held in LDS at once
     static constexpr int LDS_ELEMS = lds_elems(NCL);
     static_assert(LDS_ELEMS * sizeof(cpx<T>) <= kLdsMax, "exchange buffer exceeds the LDS");
@@ -390,8 +390,8 @@ struct LineFFT {
             const int k = jj % Ns;
 #pragma unroll
             for (int r = 1; r < Rp; ++r) {
-                // RULE 2: registers are short, so a few twiddles at a time
-                if constexpr (RULE == 2) {
+                // kSeqAlways: registers are short, so a few twiddles at a time
+                if constexpr (RULE == kSeqAlways) {
                     if (r % 3 == 1) __builtin_amdgcn_sched_barrier(0);
                 }
                 const cpx<T> w = PP ? tw[tw_off(PASS) + (r - 1) * Ns + k] : tw[r * k * (N / (Ns * Rp))];
@@ -401,7 +401,7 @@ struct LineFFT {
             }
 #pragma unroll
             for (int cc = 0; cc < NV * CPT; ++cc) {
-                if constexpr (RULE == 2) __builtin_amdgcn_sched_barrier(0);
+                if constexpr (RULE == kSeqAlways) __builtin_amdgcn_sched_barrier(0);
                 dft<T, Rp, INV>(&v[cc][t * Rp]);
             }
         }
@@ -418,7 +418,7 @@ struct LineFFT {
                                                const cpx<T>* __restrict__ tw) {
 #pragma unroll
         for (int cc = 0; cc < NV * CPT; ++cc) {
-            if constexpr (RULE == 2) __builtin_amdgcn_sched_barrier(0);
+            if constexpr (RULE == kSeqAlways) __builtin_amdgcn_sched_barrier(0);
             dft<T, R, INV>(v[cc]);
         }
         if constexpr (NPASS > 1) pass<INV, PP, 1, NB, FIRST, NV>(v, lds, c, tw);

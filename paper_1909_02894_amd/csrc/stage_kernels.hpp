@@ -245,7 +245,7 @@ constexpr int stage_buffers() {
 // the 2x2 mixes are written per output component as (own, other) expressions
 // that are the same whether the other component sits in the same thread
 // (CPT = 2) or in the partner lane (CPT = 1), so results do not depend on L or CPT.
-template <typename T, int N, int R, int L, bool COLS, int MODE, int CPT, int NB = 1, int RULE = 1>
+template <typename T, int N, int R, int L, bool COLS, int MODE, int CPT, int NB = 1, int RULE = kSeqTight>
 __device__ __forceinline__ void stage_tile(const StageParams<T>& p, int tile, cpx<T>* lds, cpx<T>* twl) {
     using F = LineFFT<T, N, R, L, COLS, CPT, RULE>;
     using TS = TwStage<T, N>;
@@ -461,7 +461,7 @@ constexpr int stream_from_tiles(int mode) { return mode == 0 ? kStreamGroups + 1
 // Results are bitwise those of stage_tile: every operation on a line is the same.
 template <typename T, int N, int R, int L, int MODE>
 __global__ void __launch_bounds__((N / R) * L) stage_stream_kernel(StageParams<T> p) {
-    using F = LineFFT<T, N, R, L, true, 2, 2>;
+    using F = LineFFT<T, N, R, L, true, 2, kSeqAlways>;
     constexpr int P = F::P;
     constexpr bool BLEND = MODE != 0, WIDE = sizeof(T) == 8;
     using raw = std::conditional_t<WIDE, d2v, f4v>;

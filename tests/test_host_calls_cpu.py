@@ -145,3 +145,16 @@ for prec, n2, sy, n1, modes in cases:
         fn, grid = column_launch(n1, n2, prec, kind, sy)
         assert (fn != plain[0]) == streams and grid == (256 if streams else n1 // sy[1]), (prec, n1, n2, kind, grid)
 """)
+
+
+def test_default_store_modes(run):
+    # the defaults dirac.h states, by shape
+    run("""
+for n1, n2, prec, scheme, mode in ((64, 64, 0, 0, 3), (512, 512, 0, 0, 3), (1024, 1024, 0, 0, 1), (1024, 1024, 1, 0, 3),
+                                   (2048, 1024, 0, 0, 0), (4096, 16, 0, 0, 0), (4096, 64, 1, 0, 0), (64, 512, 0, 0, 1),
+                                   (256, 512, 0, 0, 3), (2048, 256, 1, 0, 3), (16, 2048, 1, 0, 1),
+                                   (512, 1024, 1, D.SCHEME_EXP_SPLIT_2BIS, 1), (512, 512, 0, D.SCHEME_EXP_SPLIT_2BIS, 3)):
+    h, buf = solver(n1, n2, prec, scheme=scheme)
+    assert store_mode(h) == mode, (n1, n2, prec, scheme, store_mode(h))
+    assert D.lib.dirac_destroy(h) == 0
+""")
