@@ -129,9 +129,13 @@ __device__ __forceinline__ void batch_tile(const BatchDesc<T>& d, int tile, int 
 // Phase kernel of one size group: the workgroup -> (solve, tile) map is a
 // binary search in the group's tile prefix.  One instantiation per (n,
 // schedule) keeps each kernel's register allocation to what its own schedule
-// needs (a kernel covering every size would take the largest).
+// needs (a kernel covering every size would take the largest).  At most 256 registers,
+// so that two workgroups share a compute unit: the FP64 kernels of 128 points with both
+// components per thread took 264 (rows) and 258, and a batch of 64 solves of 128^2
+// 55.2 us per step; held to 256 (32 bytes of scratch) and 210, 43.2 (256 solves 205.8 / 151.6;
+// the kernels of every other length stay below by themselves).
 template <typename T, bool COLS, int N, int S>
-__global__ void __launch_bounds__(kBatchThreads) batch_group_kernel(BatchPhase<T> ph) {
+__global__ void __launch_bounds__(kBatchThreads, 2) batch_group_kernel(BatchPhase<T> ph) {
     extern __shared__ __align__(16) char smem[];
     const int t = xcd_tile(blockIdx.x, gridDim.x);
     if (t >= ph.total_tiles) return;
