@@ -158,3 +158,15 @@ for n1, n2, prec, scheme, mode in ((64, 64, 0, 0, 3), (512, 512, 0, 0, 3), (1024
     assert store_mode(h) == mode, (n1, n2, prec, scheme, store_mode(h))
     assert D.lib.dirac_destroy(h) == 0
 """)
+
+
+def test_defaults_of_8192_point_columns(run):
+    # one line per workgroup until there are enough of them (grids of many lines take
+    # gigabytes: their side of the rule is timed and tested on the GPU)
+    run("""
+for kind in ("flat", "layer", "curved"):
+    for n1 in (16, 64, 256, 512):
+        h, buf = solver(n1, 8192, 1, kind)
+        assert schedule(h, 1) == ((16, 2, 2) if kind == "curved" and n1 >= 512 else (16, 1, 2)), (kind, n1)
+        assert D.lib.dirac_destroy(h) == 0
+""")
