@@ -299,8 +299,9 @@ dirac_status dirac_set_schedule(dirac_solver* s, int32_t direction, const dirac_
  * small grids whose kernels are latency-bound and loses on large streaming ones.
  * The default is write-through for states up to 32 MB (the FP64 y kernel: 16 MB), but
  * ordinary stores for both kernels of grids with n1 >= 4096, and for the y kernel of
- * n2 > 256 with n1 < 256 and of the corrected second-order step with n2 > 512;
- * dirac_get_store_mode tells which.  dirac_autotune measures both per direction and
+ * n2 > 256 with n1 < 256 and of the corrected second-order step with n2 > 512; with
+ * potentials inside the direction kernels up to 32 MB (FP64: 8 MB), the y kernel only
+ * for n2 <= 256.  dirac_get_store_mode tells which.  dirac_autotune measures both per direction and
  * keeps the faster.  Results are bitwise the same either way.  Every form of
  * Scheme II's directional step (Scheme I: always 0); write-through for the y
  * kernel only with n2 <= 1024 (else DIRAC_E_ARG). */

@@ -301,6 +301,12 @@ bool pick_store_mode(int prec, int n, int dir, int other, int mode) {
     // longer than 256 points of a grid narrower than 256 are few, and written through
     // in pieces of a cache line: 64 x 512 FP64 9.6 / 10.2.
     const size_t bytes = (size_t)n * other * 4 * (prec == DIRAC_FP32 ? 4 : 8);
+    // The direction kernels with the potentials' exponentials inside are bound by those
+    // sooner: FP64 rows gain up to 8 MB, columns up to 256 points (us per step, ordinary /
+    // rows / both written through: FP64 512^2 36.1 / 30.5 / 31.6, 1024 x 256 33.2 / 30.6 / 28.4,
+    // 2048 x 256 44.6 / 47.3 / 48.7, 512 x 1024 44.7 / 45.6 / 51.1; FP32 2048 x 256 35.1 / 31.6 / 29.4,
+    // 1024^2 45.9 / 44.4 / 49.9, 2048 x 1024 111 / 109 / 117).
+    if (mode & 8) return bytes <= size_t(prec == DIRAC_FP32 ? 32 : 8) << 20 && (dir == 0 || n <= 256);
     // The corrected second-order step's columns beyond 512 points are one-line
     // tiles with both components per thread (FP32 1024^2 49.3 / 54.8).
     if ((mode & 4) && dir == 1 && n > 512) return false;

@@ -170,3 +170,20 @@ for kind in ("flat", "layer", "curved"):
         assert schedule(h, 1) == ((16, 2, 2) if kind == "curved" and n1 >= 512 else (16, 1, 2)), (kind, n1)
         assert D.lib.dirac_destroy(h) == 0
 """)
+
+
+def test_store_modes_of_potentials_inside_the_direction_kernels(run):
+    run("""
+for n1, n2, prec, inside, apart in ((512, 1024, 0, 0, 3), (2048, 256, 0, 0, 3), (1024, 1024, 0, 0, 1), (512, 512, 0, 1, 3),
+                                    (1024, 256, 0, 3, 3), (1024, 1024, 1, 1, 3), (2048, 256, 1, 3, 3)):
+    V = np.zeros((n2, n1))
+    g, m, p, _ = D.make_structs(n1, n2, 20.0, 20.0, 1e-4, 1.0, 0.5)
+    em, keep = D.make_em(n1, n2, V=V)
+    sc = D.Scheme(0, 0, 0, 0, 0.0)
+    buf = np.zeros(D.footprint_bytes_ex(g, m, p, prec, sc, em), np.uint8)
+    h = D.create_solver(g, m, p, prec, sc, em, buf.ctypes.data, buf.size, None)
+    for form, mode in ((1, inside), (2, apart)):
+        assert D.lib.dirac_set_potential_form(h, form) == 0
+        assert store_mode(h) == mode, (n1, n2, prec, form, store_mode(h))
+    assert D.lib.dirac_destroy(h) == 0
+""")
