@@ -130,6 +130,9 @@ def roofline_for(spec, kind, precision, r):
     inst = (f"stage_kernel<{'double' if precision == 0 else 'float'}, {spec.n1 if dom == 0 else spec.n2}, {rr}, "
             f"{ll}, {'true' if dom == 1 else 'false'}, {mode}, {cc}>")
     tr = load_traffic(name, inst)
+    if tr is None and dom == 1:         # a streamed column launch of that schedule
+        tr = load_traffic(name, f"stage_stream_kernel<{'double' if precision == 0 else 'float'}, {spec.n2}, {rr}, {ll}, "
+                                f"{mode}>")
     sz = 8 if precision == 0 else 4
     working = N * (8 * sz if kind != "curved" else 13 * sz)       # state + per-point tables
     bound = "hbm" if working > INFINITY_CACHE_BYTES else "cache-resident"

@@ -73,8 +73,8 @@ __device__ __forceinline__ void load_erec(const T* E, uint32_t idx, T (&e)[5]) {
 // (pairs transformed one after the other through one buffer): half the registers
 // (226 -> 152 VGPRs for curved FP64 128-point columns, 2 -> 3 waves per SIMD), half the
 // barriers, and every load of the tile issued before the first wait.  Bound by
-// memory: us per step, before / now: 128^3 FP64 curved 268 / 181 (956 MB, 5.3 TB/s),
-// FP32 127 / 98, 64^3 FP64 58 / 41, 256 x 256 x 128 FP32 flat 299 / 257.
+// memory: us per step, before / now: 128^3 FP64 curved 264 / 175 (956 MB, 5.5 TB/s),
+// FP32 125 / 95, 64^3 FP64 54 / 39, 256 x 256 x 128 FP32 flat 285 / 247.
 template <typename T, int N, int DIR, int MODE>
 __global__ void __launch_bounds__(d3_threads<T>(N)) d3_stage_kernel(D3Params<T> p) {
     constexpr int R = d3_radix<T>(N), L = d3_lines<T>(N);

@@ -47,6 +47,8 @@ def kernel_sources_digest() -> str:
 
 
 _STAGE = re.compile(r"(?<![a-z0-9_])stage_kernel<(double|float), (\d+), (\d+), (\d+), (true|false), (\d), (\d)>")
+# the streamed column kernel (T, N, R, L, MODE)
+_STREAM = re.compile(r"(?<![a-z0-9_])stage_stream_kernel<(double|float), (\d+), (\d+), (\d+), (\d)>")
 
 
 def bench_name(kernel: str, grid: str):
@@ -54,9 +56,14 @@ def bench_name(kernel: str, grid: str):
     'void dirac::stage_kernel<double, 512, 8, 2, true, 2, 1>(...)' ->
     'y_stage_f64_512x512_curved' (template arguments T, N, R, L, COLS, MODE, CPT)."""
     m = _STAGE.search(kernel)
-    if not m:
-        return None
-    t, n, r, lines, cols, mode, cpt = m.groups()
+    if m:
+        t, n, r, lines, cols, mode, cpt = m.groups()
+    else:
+        m = _STREAM.search(kernel)
+        if not m:
+            return None
+        t, n, r, lines, mode = m.groups()
+        cols = "true"
     if grid == "square":                  # every solve in the run is n x n
         grid = f"{n}x{n}"
     return f"{'y' if cols == 'true' else 'x'}_stage_{'f64' if t == 'double' else 'f32'}_{grid}_{MODE_NAMES[int(mode)]}"

@@ -23,7 +23,7 @@ def D():
     (0, 512, 256, "l"), (0, 256, 512, "l"), (0, 2048, 256, "l"), (0, 2048, 512, "l"), (0, 512, 1024, "l"),
     (0, 1024, 1024, "lcf"), (0, 2048, 1024, "lcf"), (0, 4096, 256, "lf"), (0, 4096, 512, "lf"),
     (1, 1024, 256, "l"), (1, 256, 1024, "l"), (1, 2048, 512, "l"), (1, 2048, 1024, "l"), (1, 512, 4096, "lcf"),
-    (1, 1024, 4096, "lcf"), (1, 2048, 2048, "l")])
+    (1, 1024, 4096, "lcf"), (1, 2048, 2048, "l"), (1, 64, 8192, "lcf"), (1, 512, 8192, "lc")])
 def test_default_thresholds(D, prec, n1, n2, kinds):
     for k in kinds:
         print(f"[layer shapes] {n1}x{n2} prec={prec} {k}", flush=True)
